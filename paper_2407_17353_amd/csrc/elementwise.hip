@@ -1,6 +1,7 @@
 // HBM-bound kernels of the scaled-matmul epilogue and of the standalone
 // ScaledArray operations:
-//   * prologue: clears the amax word and snapshots input scale exponents;
+//   * prologue (of the rescale): clears the amax word and snapshots the input
+//     scale's exponent;
 //   * epilogue_cast: the grid-wide dependent half of the fused dynamic
 //     rescale (Section 3.3): reads the global amax, derives the power-of-two
 //     rescale exponent (rounded down), writes the output scale, and casts the
@@ -14,20 +15,18 @@
 #include "codec.h"
 #include "ew_util.h"
 #include "kernels.h"
+#include "stat_header.h"
 
 namespace scalify {
 
 constexpr int EW_THREADS = 256;
 
-__global__ void prologue_kernel(uint32_t* hdr, const float* s0, const float* s1) {
-  if (threadIdx.x == 0) {
-    hdr[0] = 0u;
-    hdr[1] = (uint32_t)(pow2_exponent(s0) + pow2_exponent(s1));
-  }
+__global__ void prologue_kernel(uint32_t* hdr, const float* s0) {
+  if (threadIdx.x == 0) stat_clear(hdr, s0, nullptr);
 }
 
-hipError_t launch_prologue(uint32_t* hdr, const float* s0, const float* s1, hipStream_t s) {
-  hipLaunchKernelGGL(prologue_kernel, dim3(1), dim3(64), 0, s, hdr, s0, s1);
+hipError_t launch_prologue(uint32_t* hdr, const float* s0, hipStream_t s) {
+  hipLaunchKernelGGL(prologue_kernel, dim3(1), dim3(64), 0, s, hdr, s0);
   return hipGetLastError();
 }
 
@@ -240,16 +239,21 @@ __device__ __forceinline__ void unpack_block(const u4 (&w)[BlockLayout<F>::W], u
 
 template <int F>
 __global__ __launch_bounds__(EW_THREADS) void amax_kernel(const void* in, int64_t n,
-                                                           uint32_t* hdr) {
+                                                           const float* in_scale,
+                                                           uint32_t* hdr, uint64_t tag) {
   using L = BlockLayout<F>;
   __shared__ uint32_t red[EW_THREADS / 64];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    stat_clear(hdr, in_scale, nullptr);
+    stat_publish(hdr, tag);
+  }
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * (EW_THREADS / 64) + (threadIdx.x >> 6);
   const int64_t waves = (int64_t)gridDim.x * (EW_THREADS / 64);
   const int64_t nb = n / 1024;
   uint32_t kmax = 0;
   int64_t b = wave;
-  for (; b + waves < nb; b += 2 * waves) {
+  auto two_blocks = [&]() {
     u4 w0[L::W], w1[L::W];
     load_block<F>(in, b, lane, w0);
     load_block<F>(in, b + waves, lane, w1);
@@ -260,7 +264,34 @@ __global__ __launch_bounds__(EW_THREADS) void amax_kernel(const void* in, int64_
     unpack_block<F>(w1, c);
 #pragma unroll
     for (int i = 0; i < 16; ++i) kmax = max(kmax, magnitude_key<F>(c[i]));
+    b += 2 * waves;
+  };
+  // The workgroup's maximum so far, to thread 0.
+  auto block_max = [&]() {
+    for (int off = 32; off > 0; off >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off, 64));
+    __syncthreads();
+    if (lane == 0) red[threadIdx.x >> 6] = kmax;
+    __syncthreads();
+    uint32_t k = red[0];
+    for (int w = 1; w < EW_THREADS / 64; ++w) k = max(k, red[w]);
+    return __uint_as_float(to_bits<F>(k));
+  };
+  // A workgroup with several rounds of blocks folds its maximum in after the
+  // first, while it has more to load, and learns how large the others' are:
+  // at the end, when all of them finish together, almost none has anything
+  // larger to add. (2048 atomics on one word take 23 us: 180 MB of fp32 were
+  // read in 36 us with one per workgroup at the end.)
+  float known = -1.0f;
+  const bool early = (int64_t)blockIdx.x * (EW_THREADS / 64) + EW_THREADS / 64 - 1 + 3 * waves < nb;
+  if (early) {
+    two_blocks();
+    const float m = block_max();
+    if (threadIdx.x == 0) {
+      stat_await(hdr, tag);
+      known = fmaxf(stat_fold(hdr, m), m);
+    }
   }
+  while (b + waves < nb) two_blocks();
   if (b < nb) {
     u4 w0[L::W];
     load_block<F>(in, b, lane, w0);
@@ -272,13 +303,10 @@ __global__ __launch_bounds__(EW_THREADS) void amax_kernel(const void* in, int64_
   if (blockIdx.x == 0)
     for (int64_t e = nb * 1024 + threadIdx.x; e < n; e += EW_THREADS)
       kmax = max(kmax, magnitude_key<F>(load1<F>(in, e)));
-  for (int off = 32; off > 0; off >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off, 64));
-  if (lane == 0) red[threadIdx.x >> 6] = kmax;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t k = red[0];
-    for (int w = 1; w < EW_THREADS / 64; ++w) k = max(k, red[w]);
-    atomicMax(hdr, to_bits<F>(k));
+  const float m = block_max();
+  if (threadIdx.x == 0 && m > known) {
+    stat_await(hdr, tag);
+    stat_fold(hdr, m);
   }
 }
 
@@ -290,13 +318,14 @@ static int ew_grid(int64_t n) {
   return (int)g;
 }
 
-hipError_t launch_amax(const void* in, int in_dtype, int64_t n, uint32_t* hdr, hipStream_t s) {
+hipError_t launch_amax(const void* in, int in_dtype, int64_t n, const float* in_scale, uint32_t* hdr,
+                       uint64_t tag, hipStream_t s) {
   const dim3 g(ew_grid(n)), b(EW_THREADS);
   switch (in_dtype) {
-    case kE4M3: hipLaunchKernelGGL((amax_kernel<kE4M3>), g, b, 0, s, in, n, hdr); break;
-    case kE5M2: hipLaunchKernelGGL((amax_kernel<kE5M2>), g, b, 0, s, in, n, hdr); break;
-    case kF16: hipLaunchKernelGGL((amax_kernel<kF16>), g, b, 0, s, in, n, hdr); break;
-    default: hipLaunchKernelGGL((amax_kernel<kF32>), g, b, 0, s, in, n, hdr); break;
+    case kE4M3: hipLaunchKernelGGL((amax_kernel<kE4M3>), g, b, 0, s, in, n, in_scale, hdr, tag); break;
+    case kE5M2: hipLaunchKernelGGL((amax_kernel<kE5M2>), g, b, 0, s, in, n, in_scale, hdr, tag); break;
+    case kF16: hipLaunchKernelGGL((amax_kernel<kF16>), g, b, 0, s, in, n, in_scale, hdr, tag); break;
+    default: hipLaunchKernelGGL((amax_kernel<kF32>), g, b, 0, s, in, n, in_scale, hdr, tag); break;
   }
   return hipGetLastError();
 }
@@ -343,11 +372,16 @@ __global__ __launch_bounds__(EW_THREADS) void elementwise_kernel(ElemParams p) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (p.rule == RULE_COPY) *p.out_scale = p.in_scale ? *p.in_scale : 1.0f;
     else *p.out_scale = pow2_float(e_out);
+    if (p.rule == RULE_AMAX) stat_retire(p.hdr);
   }
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * (EW_THREADS / 64) + (threadIdx.x >> 6);
   const int64_t waves = (int64_t)gridDim.x * (EW_THREADS / 64);
   const int64_t nb = p.n / 1024;
+  // After the statistic's pass the blocks read last are still in the last-level
+  // cache: the cast takes them first.
+  const bool back = p.rule == RULE_AMAX;
+  auto at = [&](int64_t b) { return back ? nb - 1 - b : b; };
   auto cast_block = [&](const u4 (&w)[L::W], int64_t b) {
     uint32_t c[16];
     unpack_block<INF>(w, c);
@@ -360,15 +394,15 @@ __global__ __launch_bounds__(EW_THREADS) void elementwise_kernel(ElemParams p) {
   int64_t b = wave;
   for (; b + waves < nb; b += 2 * waves) {
     u4 w0[L::W], w1[L::W];
-    load_block<INF>(p.in, b, lane, w0);
-    load_block<INF>(p.in, b + waves, lane, w1);
-    cast_block(w0, b);
-    cast_block(w1, b + waves);
+    load_block<INF>(p.in, at(b), lane, w0);
+    load_block<INF>(p.in, at(b + waves), lane, w1);
+    cast_block(w0, at(b));
+    cast_block(w1, at(b + waves));
   }
   if (b < nb) {
     u4 w0[L::W];
-    load_block<INF>(p.in, b, lane, w0);
-    cast_block(w0, b);
+    load_block<INF>(p.in, at(b), lane, w0);
+    cast_block(w0, at(b));
   }
   if (blockIdx.x == 0)
     for (int64_t e = nb * 1024 + threadIdx.x; e < p.n; e += EW_THREADS)

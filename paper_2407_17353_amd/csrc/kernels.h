@@ -93,8 +93,9 @@ hipError_t launch_mx_pack(const uint8_t* src, int rows, int K, int ld, uint8_t* 
 hipError_t launch_gemm(const GemmParams& p, bool a_mn, bool b_kc, int fa, int fb, int epi,
                        bool fuse, hipStream_t s);
 
-// Prologue: hdr[0] = 0, hdr[1] = exponent(s0) + exponent(s1) (NULL = scale 1).
-hipError_t launch_prologue(uint32_t* hdr, const float* s0, const float* s1, hipStream_t s);
+// Header of a rescale without a statistic: hdr[0] = 0, hdr[1] = exponent(s0)
+// (NULL = scale 1).
+hipError_t launch_prologue(uint32_t* hdr, const float* s0, hipStream_t s);
 
 // Prologue of the matmul: hdr[0] = hdr[5] = hdr[6] = hdr[7] = 0 and hdr[1] =
 // e_w, the scale exponent of the pre-cast value: e_a + e_b, or with a
@@ -147,11 +148,13 @@ struct ElemParams {
   int rule;          // RULE_AMAX: from hdr amax; RULE_KEEP: e_out = e_in; RULE_FIXED: e_out = e_fixed;
                      // RULE_COPY: shift 0 and the raw input scale value is copied
   int target, sat, e_fixed;
-  const uint32_t* hdr;      // RULE_AMAX / RULE_KEEP (e_in snapshot); may be NULL otherwise
+  uint32_t* hdr;            // RULE_AMAX (whose tag is taken out), RULE_KEEP (e_in snapshot) or NULL
   const float* in_scale;    // read directly when hdr is NULL
   float* out_scale;
 };
-hipError_t launch_amax(const void* in, int in_dtype, int64_t n, uint32_t* hdr, hipStream_t s);
+// The header's statistic and exponent snapshot of in_scale (stat_header.h).
+hipError_t launch_amax(const void* in, int in_dtype, int64_t n, const float* in_scale, uint32_t* hdr,
+                       uint64_t tag, hipStream_t s);
 hipError_t launch_elementwise(const ElemParams& p, int in_dtype, int out_dtype, hipStream_t s);
 
 }  // namespace scalify

@@ -23,6 +23,9 @@ struct LnParams {
   float eps;
   int sat, target, mode;  // backward rescale: mode 1 = amax, 0 = none
   uint32_t* hdr;        // backward: workspace header
+  uint64_t tag;         // backward: the call's tag in it (stat_header.h)
+  const float* s_dy;    // backward: scales of dy and x (NULL = 1)
+  const float* s_x;
   float* partial;       // backward: per-row numbers [R][4], then [row tiles][2][stride]
   float* out_scale;
   float* amax_out;      // backward: optional amax of |dx|
@@ -38,7 +41,20 @@ __host__ __device__ inline int64_t layernorm_param_stride(int64_t D) { return (D
 // per-row-tile partial parameter gradients.
 int64_t layernorm_ws_floats(int64_t R, int64_t D);
 hipError_t launch_layernorm_fwd(const LnParams& p, int out_dtype, hipStream_t s);
-hipError_t launch_layernorm_bwd(const LnParams& p, const float* s_dy, const float* s_x,
-                                int out_dtype, hipStream_t s);
+hipError_t launch_layernorm_bwd(const LnParams& p, int out_dtype, hipStream_t s);
+
+// Families, each input format in a source file of its own:
+//   launch_ln_fwd_rows, launch_ln_bwd_rows: rows read once (layernorm_rows.h);
+//   launch_ln_apply: the backward's cast of dx and partial parameter sums.
+template <int XF>
+void launch_ln_fwd_rows(const LnParams& p, int out_dtype, hipStream_t s);
+template <int XF>
+void launch_ln_bwd_rows(const LnParams& p, hipStream_t s);
+template <int XF>
+void launch_ln_apply(const LnParams& p, int out_dtype, hipStream_t s);
+// Waves per row of the row kernels, and their workgroups for `wpr`.
+inline int ln_wpr(int D) { return D <= 2048 ? 1 : (D <= 4096 ? 2 : 4); }
+int ln_rows_grid(int64_t R, int wpr, int per_cu);
+int64_t layernorm_row_tiles(int64_t R);
 
 }  // namespace scalify

@@ -6,7 +6,9 @@
 
 #include <stdlib.h>
 
+#include <atomic>
 #include <mutex>
+#include <random>
 
 #include "../../include/scalify.h"
 #include "kernels.h"
@@ -64,6 +66,19 @@ bool single_pass_choice(int64_t tiles, int grid) {
   if (v && v[0] == '1' && v[1] == 0) return true;
   if (v && v[0] == '0' && v[1] == 0) return false;
   return tiles <= grid;
+}
+
+// Tag of a call (stat_header.h): never zero, different for every call of the
+// process, and not what a workspace holds by chance.
+uint64_t next_tag() {
+  static std::atomic<uint64_t> next{[] {
+    std::random_device rd;
+    return ((uint64_t)rd() << 32) ^ rd();
+  }()};
+  uint64_t t;
+  do t = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+  while (t == 0);
+  return t;
 }
 
 // The 4-wave kernel is persistent (one workgroup per CU walks its tiles)
@@ -457,17 +472,24 @@ scalify_status scalify_rescale(const scalify_scaled_array* in, scalify_scaled_ar
   hipStream_t s = (hipStream_t)stream;
   uint32_t* hdr = (uint32_t*)workspace;
   const int64_t n = in->rows * in->cols;
-  if (launch_prologue(hdr, in->scale, nullptr, s) != hipSuccess) return SCALIFY_ERR_HIP;
-  if (mode == SCALIFY_RESCALE_AMAX && n > 0)
-    if (launch_amax(in->data, in->dtype, n, hdr, s) != hipSuccess) return SCALIFY_ERR_HIP;
+  // The statistic's kernel keeps the header itself; without one, a header is
+  // needed only for a snapshot of an input scale that the output scale overwrites.
+  const bool stat = mode == SCALIFY_RESCALE_AMAX && n > 0;
+  const bool snapshot = stat || in->scale == out->scale;
+  if (stat) {
+    if (launch_amax(in->data, in->dtype, n, in->scale, hdr, next_tag(), s) != hipSuccess)
+      return SCALIFY_ERR_HIP;
+  } else if (snapshot) {
+    if (launch_prologue(hdr, in->scale, s) != hipSuccess) return SCALIFY_ERR_HIP;
+  }
   ElemParams p = {};
   p.in = in->data;
   p.out = out->data;
   p.n = n;
-  p.rule = mode == SCALIFY_RESCALE_AMAX ? RULE_AMAX : RULE_KEEP;
+  p.rule = stat ? RULE_AMAX : RULE_KEEP;
   p.target = target_log2;
   p.sat = saturate != 0;
-  p.hdr = hdr;
+  p.hdr = snapshot ? hdr : nullptr;
   p.in_scale = in->scale;
   p.out_scale = out->scale;
   if (launch_elementwise(p, in->dtype, out->dtype, s) != hipSuccess) return SCALIFY_ERR_HIP;
@@ -590,12 +612,15 @@ scalify_status scalify_layernorm_bwd(const scalify_scaled_array* dy, const scali
   p.target = target_log2;
   p.mode = rescale == SCALIFY_RESCALE_AMAX ? 1 : 0;
   p.hdr = (uint32_t*)workspace;
+  p.tag = next_tag();
+  p.s_dy = dy->scale;
+  p.s_x = x->scale;
   p.partial = (float*)((uint8_t*)workspace + kHeaderBytes);
   p.out_scale = dx->scale;
   p.amax_out = amax_out;
   p.dgamma = dgamma;
   p.dbeta = dbeta;
-  if (launch_layernorm_bwd(p, dy->scale, x->scale, dx->dtype, (hipStream_t)stream) != hipSuccess)
+  if (launch_layernorm_bwd(p, dx->dtype, (hipStream_t)stream) != hipSuccess)
     return SCALIFY_ERR_HIP;
   return SCALIFY_OK;
 }
