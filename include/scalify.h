@@ -252,17 +252,20 @@ size_t scalify_matmul_workspace_size_opts(int64_t M, int64_t N, const scalify_ma
  * not shared with a concurrent call. Determinism: reruns are bit-identical.
  * M, N or K may be 0 (K = 0 gives an all-zero output).
  *
- * AMAX without a fused epilogue, on an output of at most one 256 x 256 tile
- * per compute unit, runs as one GEMM kernel (the single pass): its
- * workgroups hold their output tile in the matrix cores' accumulators, meet
- * at a grid barrier on the amax statistic, and cast; the output scale and
- * amax_out are written by that kernel. Larger outputs take the GEMM + cast
- * kernel pair (faster there). The barrier's wait is bounded: if the grid is
+ * AMAX on an output small enough that every workgroup holds its tiles (tiles
+ * of 256 x 256, fewer rows or columns on smaller outputs, one per compute
+ * unit; not with a fused epilogue on outputs of more than half that) runs as
+ * one GEMM kernel (the single pass): its workgroups keep their output tiles in
+ * registers or LDS, meet at a grid barrier on the amax statistic, and cast;
+ * the output scale and amax_out are written by that kernel. Larger outputs
+ * take the GEMM + cast kernel pair (faster there). The barrier's wait is bounded: if the grid is
  * not co-resident on the GPU (other work occupies its compute units), the
  * workgroups fall back to casting from the intermediate after the wait, with
  * the same result, later. Environment (read at each call):
- * SCALIFY_SINGLE_PASS=1 takes the single pass at any size, =0 never (it
- * does not cover block-scaled calls with a.trans = 1 and b.trans = 0);
+ * SCALIFY_SINGLE_PASS=1 takes the single pass wherever it can run (any size of
+ * a plain or block-scaled call, except block scales with a.trans = 1 and
+ * b.trans = 0 on outputs of more than two 64 x 64 tiles per compute unit), =0
+ * never;
  * SCALIFY_SPIN_TICKS=<n> sets the barrier's wait in ticks of the
  * GPU's 100 MHz counter (default 20 ms plus 4 us per 128 of K; 0 exercises
  * the fallback). SCALIFY_PERSISTENT=0 launches one workgroup per tile (and no

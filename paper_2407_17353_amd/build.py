@@ -4,14 +4,19 @@ Every .hip source under csrc/ is compiled by hipcc in parallel and linked into
 one shared library next to this file. Packed-fp32 instructions are disabled
 for all device code.
 
-The one-wave-per-SIMD GEMM kernels keep their accumulators in AGPRs that only
-their inline asm names (AccTile in csrc/gemm_kernel.h); the compiler does not
-know these registers hold values. The build therefore disassembles the GEMM
-objects and fails if, in any kernel that uses those accumulators, any
+The GEMM kernels with many accumulators keep them in AGPRs that only their
+inline asm names (AccTile in csrc/gemm_kernel.h); the compiler does not know
+these registers hold values. The build therefore disassembles the objects of
+these kernels and fails if, in any kernel that uses those accumulators, any
 instruction other than the accumulator asm's own forms (an MFMA whose
 destination and C operand are the same a[n:n+3], a write of 0, a read into a
-VGPR) names an AGPR -- the compiler spilling into AGPRs or using one as the
+VGPR) names one of them -- the compiler spilling into it or using it as the
 data of a load or an MFMA operand -- or the kernel uses scratch memory.
+
+The loads of these kernels are inline asm too, so the compiler does not keep
+the distance their scalar operands need: the build fails if a vector memory
+instruction reads a scalar register that a vector instruction wrote less than
+five wait states before.
 """
 from __future__ import annotations
 
@@ -66,10 +71,58 @@ def _asm_agpr_form(insn: str) -> bool:
     return bool(_ASM_ZERO.match(insn) or _ASM_READ.match(insn))
 
 
-def check_accumulator_isolation(obj: str, tmp: str) -> int:
+def _sgprs(text: str) -> set:
+    """The scalar registers a piece of an instruction names."""
+    regs = set()
+    for m in re.finditer(r"\bs(\d+)\b|\bs\[(\d+):(\d+)\]", text):
+        lo, hi = (m.group(1),) * 2 if m.group(1) else (m.group(2), m.group(3))
+        regs.update(range(int(lo), int(hi) + 1))
+    return regs
+
+
+def scalar_distance_violations(insns) -> list:
+    """Vector memory instructions that read a scalar register less than five
+    wait states after a vector instruction wrote it (straight-line scan)."""
+    bad, recent = [], []
+    for insn in insns:
+        if not insn:
+            continue
+        op = insn.split()[0]
+        if op.startswith(("buffer_", "global_", "flat_", "scratch_")):
+            used = _sgprs(insn)
+            if any(age < 5 and used & regs for age, regs in recent):
+                bad.append(insn)
+        step = int(insn.split()[1]) + 1 if op == "s_nop" else 1
+        recent = [(age + step, regs) for age, regs in recent if age + step < 5]
+        if op.startswith("v_") and " " in insn:
+            regs = _sgprs(insn.split(None, 1)[1].split(",")[0])
+            if regs:
+                recent.append((0, regs))
+    return bad
+
+
+def _agprs(insn: str) -> set:
+    """The AGPR numbers an instruction names."""
+    regs = set()
+    for m in re.finditer(r"\ba(\d+)\b|\ba\[(\d+):(\d+)\]", insn):
+        lo, hi = (m.group(1),) * 2 if m.group(1) else (m.group(2), m.group(3))
+        regs.update(range(int(lo), int(hi) + 1))
+    return regs
+
+
+def pinned_kernel(src: str, name: str) -> bool:
+    """Whether a kernel of this source keeps its accumulators in asm-named
+    AGPRs: every MFMA kernel of the gemm_* sources, and of the mid_* sources
+    those with 256 columns (8 accumulator tiles per row of tiles)."""
+    base = os.path.basename(src)
+    return base.startswith("gemm_") or (base.startswith("mid_") and "ELi8ELi3EEEv" in name)
+
+
+def check_code(obj: str, tmp: str) -> int:
     """Disassemble the gfx950 code of one object and check every kernel that
-    keeps accumulators in asm-named AGPRs. Returns the number of such
-    kernels; raises RuntimeError on a violation."""
+    keeps accumulators in asm-named AGPRs, and every function's scalar
+    operands of vector memory. Returns the number of kernels with such
+    accumulators; raises RuntimeError on a violation."""
     base = os.path.join(tmp, os.path.basename(obj))
     subprocess.run([_llvm("llvm-objcopy"), f"--dump-section=.hip_fatbin={base}.fatbin", obj],
                    check=True, capture_output=True)
@@ -89,22 +142,26 @@ def check_accumulator_isolation(obj: str, tmp: str) -> int:
             kernels[name].append(line)
     checked = 0
     for name, body in kernels.items():
-        if not any(_AGPR_MFMA.search(l) for l in body):
-            # Every other function (the 8-wave kernels, and the out-of-line
-            # casts the 4-wave epilogues call while accumulators still sit in
-            # AGPRs) must leave AGPRs alone.
-            bad = [l.strip() for l in body if _ANY_AGPR.search(l.split("//")[0])]
-            if bad:
+        insns = [line.split("//")[0].strip() for line in body]
+        near = scalar_distance_violations(insns)
+        if near:
+            raise RuntimeError(f"{obj}: {name} reads a scalar register too soon: {near[:4]}")
+        if not any(_AGPR_MFMA.search(l) for l in insns):
+            # Out-of-line functions that the kernels call while accumulators
+            # still sit in AGPRs must leave AGPRs alone.
+            bad = [l for l in insns if _ANY_AGPR.search(l)]
+            if bad and os.path.basename(obj).startswith("gemm_"):
                 raise RuntimeError(f"{obj}: function {name} uses AGPRs: {bad[:4]}")
             continue
+        if not pinned_kernel(obj, name):
+            continue
         checked += 1
-        bad = []
-        for line in body:
-            insn = line.split("//")[0].strip()
-            if "scratch_" in insn:
-                bad.append(insn)
-            elif _ANY_AGPR.search(insn) and not _asm_agpr_form(insn):
-                bad.append(insn)
+        held = set()
+        for insn in insns:
+            if _AGPR_MFMA.search(insn):
+                held |= _agprs(insn)
+        bad = [insn for insn in insns
+               if "scratch_" in insn or (_agprs(insn) & held and not _asm_agpr_form(insn))]
         if bad:
             raise RuntimeError(f"{obj}: kernel {name} has compiler-placed AGPR or scratch "
                                f"accesses next to the asm-held accumulators: {bad[:4]}")
@@ -123,8 +180,8 @@ def build(verbose: bool = False) -> str:
                 raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
             if verbose and r.stderr.strip():
                 print(r.stderr)
-            if os.path.basename(src).startswith("gemm_"):
-                check_accumulator_isolation(obj, tmp)
+            if os.path.basename(src).startswith(("gemm_", "mid_", "wave_")):
+                check_code(obj, tmp)
             return obj
 
         workers = min(len(sources), max(1, os.cpu_count() or 1), 8)

@@ -12,6 +12,7 @@
 // Every kernel moves 16 elements per thread per iteration with 128-bit
 // loads; the cast kernel walks rows of the intermediate, the amax and
 // elementwise kernels walk 1024-element blocks (layout below).
+#include "call_header.h"
 #include "codec.h"
 #include "ew_util.h"
 #include "kernels.h"
@@ -30,49 +31,20 @@ hipError_t launch_prologue(uint32_t* hdr, const float* s0, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Matmul prologue: the scale exponent e_w of the pre-cast value (scaled add
-// rule of Algorithm 3 with a residual) and, for the delayed rescale
-// (Section 3.3), the output scale from the statistic an earlier call
-// recorded, or without a rescale the propagated scale itself, so that the
-// GEMM can cast directly; clears the statistic and the single-pass barrier.
-__global__ void matmul_prologue_kernel(uint32_t* hdr, MatmulPrologue q) {
+__global__ void empty_matmul_kernel(EmptyMatmul q) {
   if (threadIdx.x == 0) {
     const int e_ab = pow2_exponent(q.s0) + pow2_exponent(q.s1);
-    int e_w = e_ab, e_cc = q.e_c;
-    if (q.residual) {
-      // sqrt(2^(2 e_p) + 2^(2 e_q)) rounded down to a power of two is the
-      // larger of the two scales.
-      const int e_q = pow2_exponent(q.s_res);
-      e_w = max(e_ab + q.e_c, e_q);
-      e_cc = 0;
-      hdr[3] = (uint32_t)(e_ab - e_w);
-      hdr[4] = (uint32_t)(e_q - e_w);
-    }
-    hdr[0] = 0u;
-    hdr[1] = (uint32_t)e_w;
-    hdr[5] = hdr[6] = hdr[7] = 0u;
-    if (q.direct) {
-      // |statistic| of an earlier call (delayed rescale), or none (e_r = 0)
-      const uint32_t stat = q.amax_in ? __float_as_uint(*q.amax_in) & 0x7FFFFFFFu : 0u;
-      const int e_r = rescale_exponent(stat, q.target);  // 0 for 0, Inf, NaN
-      const int e_out = clamp_e8m0(e_w + e_cc + e_r);
-      hdr[2] = (uint32_t)(e_out - e_w);
-      *q.out_scale = pow2_float(e_out);
-    }
+    // (a residual's scaled add: sqrt(2^(2 e_p) + 2^(2 e_q)) rounded down is
+    // the larger of the two scales)
+    const int e_w = q.residual ? max(e_ab + q.e_c, pow2_exponent(q.s_res)) : e_ab + q.e_c;
+    const uint32_t stat = q.amax_in ? __float_as_uint(*q.amax_in) & 0x7FFFFFFFu : 0u;
+    *q.out_scale = pow2_float(clamp_e8m0(e_w + rescale_exponent(stat, q.target)));
+    if (q.amax_out) *q.amax_out = 0.0f;
   }
 }
 
-hipError_t launch_matmul_prologue(uint32_t* hdr, const MatmulPrologue& q, hipStream_t s) {
-  hipLaunchKernelGGL(matmul_prologue_kernel, dim3(1), dim3(64), 0, s, hdr, q);
-  return hipGetLastError();
-}
-
-__global__ void finalize_amax_kernel(const uint32_t* hdr, int e_c, float* amax_out) {
-  if (threadIdx.x == 0) *amax_out = __uint_as_float(hdr[0]) * pow2_float(-e_c);
-}
-
-hipError_t launch_finalize_amax(const uint32_t* hdr, int e_c, float* amax_out, hipStream_t s) {
-  hipLaunchKernelGGL(finalize_amax_kernel, dim3(1), dim3(64), 0, s, hdr, e_c, amax_out);
+hipError_t launch_empty_matmul(const EmptyMatmul& q, hipStream_t s) {
+  hipLaunchKernelGGL(empty_matmul_kernel, dim3(1), dim3(64), 0, s, q);
   return hipGetLastError();
 }
 
@@ -98,6 +70,7 @@ __global__ __launch_bounds__(EW_THREADS) void epilogue_cast_kernel(EpilogueParam
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     *p.out_scale = pow2_float(e_out);
     if (p.amax_out) *p.amax_out = __uint_as_float(amax_raw) * pow2_float(-p.e_c);
+    *(uint64_t*)(p.hdr + kHdrTag) = 0;  // the call's last use of the header
   }
   // 2-D grid: blockIdx.y walks rows, x-threads walk 16-element chunks.
   const int cpr = (p.N + 15) / 16;

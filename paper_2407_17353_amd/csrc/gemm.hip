@@ -18,44 +18,43 @@ int gemm4_grid(int tiles) {
   return tiles < n ? tiles : n;
 }
 
-hipError_t launch_gemm(const GemmParams& p_in, bool a_mn, bool b_kc, int fa, int fb, int epi,
-                       bool fuse, hipStream_t s) {
-  if (p_in.tiles_m * p_in.tiles_n == 0) return hipSuccess;
-  GemmParams p = p_in;
-  p.epi = epi;
+hipError_t launch_gemm(const GemmParams& p, bool a_mn, bool b_kc, int fa, int fb, hipStream_t s) {
   if (p.mx_a) {
-    if (mx_on_8_waves(a_mn, b_kc)) return launch_layout_mx<true, false>(p, fa, fb, epi, s);
+    // (A [K][M] with B [K][N]: a kernel of its own, without the single pass)
+    if (a_mn && !b_kc) return launch_layout_mx<true, false>(p, fa, fb, s);
     if (!p.single_pass) {
-      if (!a_mn && b_kc) return launch_layout_mx<false, true>(p, fa, fb, epi, s);
-      if (!a_mn && !b_kc) return launch_layout_mx<false, false>(p, fa, fb, epi, s);
-      return launch_layout_mx<true, true>(p, fa, fb, epi, s);
+      if (!a_mn && b_kc) return launch_layout_mx<false, true>(p, fa, fb, s);
+      if (!a_mn && !b_kc) return launch_layout_mx<false, false>(p, fa, fb, s);
+      return launch_layout_mx<true, true>(p, fa, fb, s);
     }
-    if (!a_mn && b_kc) return launch_layout_mx_sp<false, true>(p, fa, fb, epi, s);
-    if (!a_mn && !b_kc) return launch_layout_mx_sp<false, false>(p, fa, fb, epi, s);
-    return launch_layout_mx_sp<true, true>(p, fa, fb, epi, s);
+    if (!a_mn && b_kc) return launch_layout_mx_sp<false, true>(p, fa, fb, s);
+    if (!a_mn && !b_kc) return launch_layout_mx_sp<false, false>(p, fa, fb, s);
+    return launch_layout_mx_sp<true, true>(p, fa, fb, s);
   }
-  if (fuse) {
-    if (!a_mn && b_kc) return launch_layout<false, true, true>(p, fa, fb, epi, s);
-    if (!a_mn && !b_kc) return launch_layout<false, false, true>(p, fa, fb, epi, s);
-    if (a_mn && b_kc) return launch_layout<true, true, true>(p, fa, fb, epi, s);
-    return launch_layout<true, false, true>(p, fa, fb, epi, s);
-  }
-  if (epi == EPI_DIRECT) {
-    if (!a_mn && b_kc) return launch_layout_direct<false, true>(p, fa, fb, epi, s);
-    if (!a_mn && !b_kc) return launch_layout_direct<false, false>(p, fa, fb, epi, s);
-    if (a_mn && b_kc) return launch_layout_direct<true, true>(p, fa, fb, epi, s);
-    return launch_layout_direct<true, false>(p, fa, fb, epi, s);
+  if (p.epi == EPI_DIRECT) {
+    if (!a_mn && b_kc) return launch_layout_direct<false, true>(p, fa, fb, s);
+    if (!a_mn && !b_kc) return launch_layout_direct<false, false>(p, fa, fb, s);
+    if (a_mn && b_kc) return launch_layout_direct<true, true>(p, fa, fb, s);
+    return launch_layout_direct<true, false>(p, fa, fb, s);
   }
   if (p.single_pass) {
-    if (!a_mn && b_kc) return launch_layout_sp<false, true>(p, fa, fb, epi, s);
-    if (!a_mn && !b_kc) return launch_layout_sp<false, false>(p, fa, fb, epi, s);
-    if (a_mn && b_kc) return launch_layout_sp<true, true>(p, fa, fb, epi, s);
-    return launch_layout_sp<true, false>(p, fa, fb, epi, s);
+    if (!a_mn && b_kc) return launch_layout_sp<false, true>(p, fa, fb, s);
+    if (!a_mn && !b_kc) return launch_layout_sp<false, false>(p, fa, fb, s);
+    if (a_mn && b_kc) return launch_layout_sp<true, true>(p, fa, fb, s);
+    return launch_layout_sp<true, false>(p, fa, fb, s);
   }
-  if (!a_mn && b_kc) return launch_layout<false, true, false>(p, fa, fb, epi, s);
-  if (!a_mn && !b_kc) return launch_layout<false, false, false>(p, fa, fb, epi, s);
-  if (a_mn && b_kc) return launch_layout<true, true, false>(p, fa, fb, epi, s);
-  return launch_layout<true, false, false>(p, fa, fb, epi, s);
+  if (!a_mn && b_kc) return launch_layout<false, true>(p, fa, fb, s);
+  if (!a_mn && !b_kc) return launch_layout<false, false>(p, fa, fb, s);
+  if (a_mn && b_kc) return launch_layout<true, true>(p, fa, fb, s);
+  return launch_layout<true, false>(p, fa, fb, s);
+}
+
+hipError_t launch_fused_gemm(const GemmParams& p, bool a_mn, bool b_kc, int fa, int fb,
+                             hipStream_t s) {
+  if (!a_mn && b_kc) return launch_layout_fused<false, true>(p, fa, fb, s);
+  if (!a_mn && !b_kc) return launch_layout_fused<false, false>(p, fa, fb, s);
+  if (a_mn && b_kc) return launch_layout_fused<true, true>(p, fa, fb, s);
+  return launch_layout_fused<true, false>(p, fa, fb, s);
 }
 
 // One thread per packed 32-bit word: word ((t * G + q) * 64 + 16 g + r)

@@ -28,6 +28,7 @@
 //     tile straight from the accumulators and cast their earlier tiles from
 //     the intermediate.
 #pragma once
+#include "call_header.h"
 #include "ew_util.h"
 #include "gemm_kernel.h"
 
@@ -35,10 +36,6 @@ namespace scalify {
 
 // LDS bytes per wave for staging the epilogue's stores.
 constexpr int kStageWave = 4096;
-
-// Header words of the single-pass barrier (zeroed by the matmul prologue).
-constexpr int kHdrArrive = 5, kHdrState = 6, kHdrWritten = 7;
-enum SpState : uint32_t { SP_RUNNING = 0, SP_COMPLETE = 1, SP_ABORTED = 2 };
 
 // ---- casts without calls (usable while accumulators sit in AGPRs)
 
@@ -134,17 +131,6 @@ __device__ __forceinline__ void encode16_any(const uint32_t (&c)[16], bool fast,
   }
 }
 
-// Shift of the cast from the amax statistic (bits of max |acc|): the rescale
-// exponent of Section 3.3 rounded down, e_out = clamp(e_w + e_c + e_r).
-__device__ __forceinline__ int sp_shift(uint32_t amax_raw, int e_w, int e_c, int target,
-                                        int* e_out_p) {
-  int e_r = 0;
-  if (amax_raw != 0u && amax_raw < 0x7F800000u) e_r = floor_log2_bits(amax_raw) - e_c - target;
-  const int e_out = clamp_e8m0(e_w + e_c + e_r);
-  *e_out_p = e_out;
-  return e_out - e_w;
-}
-
 // OF: the output format the kernel casts to (EPI_DIRECT, SP), -1 for the
 // intermediate-only kernels.
 template <bool A_MN, bool B_KC, int FA, int FB, int EPI, bool MX, bool SP, int OF>
@@ -178,6 +164,9 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
   const uint32_t lda = (uint32_t)p.lda, ldb = (uint32_t)p.ldb;
   const v4i ra = make_rsrc(p.a, p.a_bytes);
   const v4i rb = make_rsrc(p.b, p.b_bytes);
+  const RawScales raw_scales = load_scales(p);
+  if (blockIdx.x == 0 && tid == 0 && p.uses_header)
+    header_clear(p, call_exponents(p, raw_scales).e_w);
 
   // Per-load parts of the load offsets, per lane (load q of this wave's share
   // of a tile: block blk = wave * BPW + q): KC rows along M/N, MC rows along
@@ -375,9 +364,9 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
   // ---- epilogue helpers: lane holds C[m][n..n+3] of tile (mi, ni) at
   // m = m0 + wm + 16 mi + (lane & 15), n = n0 + wn + 16 ni + 4 (lane >> 4)
   const bool sat = p.sat != 0;
-  const int e_w = (int)__builtin_amdgcn_readfirstlane(p.hdr[1]);
-  // EPI_DIRECT: data' = acc * 2^-shift, shift from the prologue
-  const int d_shift = EPI == EPI_DIRECT ? (int)__builtin_amdgcn_readfirstlane(p.hdr[2]) : 0;
+  const CallExponents ex = call_exponents(p, raw_scales);
+  const int e_w = ex.e_w;
+  const int d_shift = ex.shift;  // EPI_DIRECT: data' = acc * 2^-shift
   // Block-scaled accumulators may be fp32 subnormals (the plain ones never are).
   auto fast_of = [&](int sh) { return sh >= (MX ? kFastShiftMinSub : -kFastShiftMax) && sh <= kFastShiftMax; };
 
@@ -612,6 +601,7 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
   advance();
   static_for<0, MI * NI>([&](auto I) { AccTile<decltype(I)::value>::zero(); });
   wait_vmcnt<LOADS_PER_STEP + (MX ? 2 : 0)>();
+  if (blockIdx.x == 0 && tid == 0 && p.uses_header) header_publish(p);
   __syncthreads();
   if (KT_full == 0 && (krem & 15)) zero_tail(sA0, sB0);
 #pragma unroll
@@ -694,17 +684,14 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
   if constexpr (!SP) {
     if (tid == 0) {
       const float wmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-      atomicMax(p.hdr, __float_as_uint(wmax));
+      if constexpr (EPI == EPI_DIRECT)
+        direct_finish(p, wmax, G, ex.e_out);
+      else
+        pair_finish(p, wmax);
     }
     return;
   } else {
-    // Grid barrier on the statistic. Thread 0 adds the workgroup's max
-    // (atomic, performed before the arrival is counted), counts its arrival
-    // and waits for the state word: the last arrival sets it
-    // COMPLETE. The wait is bounded (p.spin_ticks of the 100 MHz real-time
-    // counter, polled every few hundred cycles): a workgroup that
-    // runs out sets ABORTED unless the state has changed; whichever of the
-    // two is set first decides for every workgroup. COMPLETE: every
+    // Grid barrier on the statistic (grid_arrive, grid_wait). COMPLETE: every
     // statistic is in, each workgroup casts its own tiles. ABORTED (the grid
     // was not co-resident): each workgroup writes its held tile to the
     // intermediate too, and the last one to have done so casts every tile.
@@ -838,22 +825,9 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
         batches(std::integral_constant<int, 2>{});
     };
     const bool own = ntiles > 1;
-    if (tid == 0) {
-      const float wmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-      __hip_atomic_fetch_max(p.hdr, __float_as_uint(wmax), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // the max is performed before the arrival is counted (nothing else of
-      // this workgroup needs to be visible to the others unless the barrier
-      // aborts, which releases its stores itself)
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      const uint32_t arrived = __hip_atomic_fetch_add(p.hdr + kHdrArrive, 1u, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT) + 1u;
-      if (arrived == (uint32_t)G) {
-        uint32_t e = SP_RUNNING;
-        __hip_atomic_compare_exchange_strong(p.hdr + kHdrState, &e, (uint32_t)SP_COMPLETE,
-                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
+    uint32_t arrived = SP_RUNNING;
+    if (tid == 0)
+      arrived = grid_arrive(p, fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), G);
     // the first batch of the earlier tiles in flight during the wait (issued
     // after the arrival, which waits for every load of its wave)
     if (own) {
@@ -861,50 +835,17 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
       tile_of(false, 0, m0, n0);
       static_for<0, CH>([&](auto I) { load_slot(I, m0, n0, 0); });
     }
-    if (tid == 0) {
-      uint32_t st = __hip_atomic_load(p.hdr + kHdrState, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // (a poll takes at least the sleep, 640 cycles or 30 ticks: the poll
-      // count bounds the wait even if the counter did not advance)
-      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-      const int64_t max_polls = p.spin_ticks / 8 + 64;
-      for (int64_t it = 0; st == SP_RUNNING && it < max_polls &&
-                           (int64_t)(__builtin_amdgcn_s_memrealtime() - t0) < p.spin_ticks;
-           ++it) {
-        __builtin_amdgcn_s_sleep(10);
-        st = __hip_atomic_load(p.hdr + kHdrState, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if (st == SP_RUNNING) {
-        uint32_t e = SP_RUNNING;
-        __hip_atomic_compare_exchange_strong(p.hdr + kHdrState, &e, (uint32_t)SP_ABORTED,
-                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        st = __hip_atomic_load(p.hdr + kHdrState, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      sp_word[0] = st;
-      sp_word[1] = __hip_atomic_load(p.hdr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (tid == 0) grid_wait(p, arrived, sp_word);
     __syncthreads();
-    const uint32_t st = sp_word[0];
+    uint32_t amax_raw = sp_word[1];
     bool cast_all = false;
-    if (st == SP_ABORTED) {
+    if (sp_word[0] == SP_ABORTED) {
       // the held tile joins the intermediate; the last writer casts everything
       float unused = 0.f;
       store_tile(OI{}, std::false_type{}, c_m0, c_n0, 0, unused);
-      // every thread's intermediate stores (all tiles of this workgroup)
-      // device-wide before the count; the last writer acquires them all
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      __syncthreads();
-      if (tid == 0) {
-        const uint32_t w = __hip_atomic_fetch_add(p.hdr + kHdrWritten, 1u, __ATOMIC_ACQ_REL,
-                                                  __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        sp_word[0] = w == (uint32_t)G ? 1u : 0u;
-        sp_word[1] = __hip_atomic_load(p.hdr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      __syncthreads();
-      if (!sp_word[0]) return;
+      if (!last_writer(p, G, sp_word, amax_raw)) return;
       cast_all = true;
     }
-    const uint32_t amax_raw = sp_word[1];
     int e_out;
     const int shift = sp_shift(amax_raw, e_w, p.e_c, p.target, &e_out);
     if (tid == 0 && (blockIdx.x == 0 || cast_all)) {
@@ -923,40 +864,34 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
 
 // ---- launches. Families, each instantiated in a source file of its own so
 // that they compile in parallel:
-//   launch_layout<A_MN, B_KC, false> (gemm_<layout>.hip): the 4-wave kernel
-//     with the intermediate (GEMM + cast kernel);
-//   launch_layout_direct<A_MN, B_KC> (gemm_<layout>_direct.hip): the 4-wave
-//     kernel with the direct cast (delayed or no rescale);
+//   launch_layout<A_MN, B_KC> (gemm_<layout>.hip): the intermediate (GEMM +
+//     cast kernel);
+//   launch_layout_direct<A_MN, B_KC> (gemm_<layout>_direct.hip): the direct
+//     cast (delayed or no rescale);
 //   launch_layout_sp<A_MN, B_KC> (gemm_<layout>_sp.hip): the single pass;
-//   launch_layout<A_MN, B_KC, true> (gemm_<layout>_fused.hip): the 8-wave
+//   launch_layout_fused<A_MN, B_KC> (gemm_<layout>_fused.hip): the 8-wave
 //     kernel with the fused residual add / activation / channel scales;
 //   launch_layout_mx<A_MN, B_KC> (gemm_<layout>_mx.hip, direct cast or the
 //   fp32 intermediate) and launch_layout_mx_sp<A_MN, B_KC>
 //   (gemm_<layout>_mx_sp.hip, single pass): MX block scales.
-template <bool A_MN, bool B_KC, bool FUSE>
-hipError_t launch_layout(const GemmParams& p, int fa, int fb, int epi, hipStream_t s);
 template <bool A_MN, bool B_KC>
-hipError_t launch_layout_direct(const GemmParams& p, int fa, int fb, int epi, hipStream_t s);
+hipError_t launch_layout(const GemmParams& p, int fa, int fb, hipStream_t s);
 template <bool A_MN, bool B_KC>
-hipError_t launch_layout_sp(const GemmParams& p, int fa, int fb, int epi, hipStream_t s);
+hipError_t launch_layout_direct(const GemmParams& p, int fa, int fb, hipStream_t s);
 template <bool A_MN, bool B_KC>
-hipError_t launch_layout_mx(const GemmParams& p, int fa, int fb, int epi, hipStream_t s);
+hipError_t launch_layout_sp(const GemmParams& p, int fa, int fb, hipStream_t s);
 template <bool A_MN, bool B_KC>
-hipError_t launch_layout_mx_sp(const GemmParams& p, int fa, int fb, int epi, hipStream_t s);
+hipError_t launch_layout_fused(const GemmParams& p, int fa, int fb, hipStream_t s);
+template <bool A_MN, bool B_KC>
+hipError_t launch_layout_mx(const GemmParams& p, int fa, int fb, hipStream_t s);
+template <bool A_MN, bool B_KC>
+hipError_t launch_layout_mx_sp(const GemmParams& p, int fa, int fb, hipStream_t s);
 
 // The persistent kernel runs p.grid workgroups (host: gemm4_grid).
 template <bool A_MN, bool B_KC, int FA, int FB, int EPI, bool MX, bool SP, int OF>
 hipError_t launch4(const GemmParams& p, hipStream_t s) {
   hipLaunchKernelGGL((gemm4_kernel<A_MN, B_KC, FA, FB, EPI, MX, SP, OF>), dim3(p.grid), dim3(256),
                      0, s, p);
-  return hipGetLastError();
-}
-
-// The 8-wave kernel: one workgroup per tile.
-template <bool A_MN, bool B_KC, int FA, int FB, int EPI, bool FUSE, bool CH, bool MX>
-hipError_t launch8(const GemmParams& p, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_kernel<A_MN, B_KC, FA, FB, EPI, FUSE, 8, CH, MX>),
-                     dim3(p.tiles_m * p.tiles_n), dim3(WaveCfg<8>::NTHR), 0, s, p);
   return hipGetLastError();
 }
 
@@ -969,22 +904,13 @@ hipError_t by_formats(const GemmParams& p, int fa, int fb, hipStream_t s) {
   return F<kE5M2, kE5M2>::run(p, s);
 }
 
-template <bool A_MN, bool B_KC, bool FUSE>
+template <bool A_MN, bool B_KC>
 struct PlainFamily {
   template <int FA, int FB>
   struct F {
     static hipError_t run(const GemmParams& p, hipStream_t s) {
-      if constexpr (FUSE) {
-        const bool ch = p.ch_a || p.ch_b;
-        if (p.epi == EPI_DIRECT)
-          return ch ? launch8<A_MN, B_KC, FA, FB, EPI_DIRECT, true, true, false>(p, s)
-                    : launch8<A_MN, B_KC, FA, FB, EPI_DIRECT, true, false, false>(p, s);
-        return ch ? launch8<A_MN, B_KC, FA, FB, EPI_INTER32, true, true, false>(p, s)
-                  : launch8<A_MN, B_KC, FA, FB, EPI_INTER32, true, false, false>(p, s);
-      } else {
-        if (p.epi == EPI_INTER16) return launch4<A_MN, B_KC, FA, FB, EPI_INTER16, false, false, -1>(p, s);
-        return launch4<A_MN, B_KC, FA, FB, EPI_INTER32, false, false, -1>(p, s);
-      }
+      if (p.epi == EPI_INTER16) return launch4<A_MN, B_KC, FA, FB, EPI_INTER16, false, false, -1>(p, s);
+      return launch4<A_MN, B_KC, FA, FB, EPI_INTER32, false, false, -1>(p, s);
     }
   };
 };
@@ -1020,20 +946,5 @@ struct SpFamily {
     }
   };
 };
-
-// MX block scales on 8 waves (A and B both stored k-major, A [K][M] and
-// B [K][N]: the 4-wave variant does not fit its registers, which the build
-// check would reject), direct cast or fp32 intermediate + cast kernel.
-template <bool A_MN, bool B_KC>
-struct Mx8Family {
-  template <int FA, int FB>
-  struct F {
-    static hipError_t run(const GemmParams& p, hipStream_t s) {
-      if (p.epi == EPI_DIRECT) return launch8<A_MN, B_KC, FA, FB, EPI_DIRECT, false, false, true>(p, s);
-      return launch8<A_MN, B_KC, FA, FB, EPI_INTER32, false, false, true>(p, s);
-    }
-  };
-};
-constexpr bool mx_on_8_waves(bool a_mn, bool b_kc) { return a_mn && !b_kc; }
 
 }  // namespace scalify

@@ -5,8 +5,8 @@
 namespace scalify {
 
 template <>
-hipError_t launch_layout<false, false, false>(const GemmParams& p, int fa, int fb, int, hipStream_t s) {
-  return by_formats<PlainFamily<false, false, false>::template F>(p, fa, fb, s);
+hipError_t launch_layout<false, false>(const GemmParams& p, int fa, int fb, hipStream_t s) {
+  return by_formats<PlainFamily<false, false>::template F>(p, fa, fb, s);
 }
 
 }  // namespace scalify

@@ -5,7 +5,7 @@
 namespace scalify {
 
 template <>
-hipError_t launch_layout_mx<false, false>(const GemmParams& p, int fa, int fb, int, hipStream_t s) {
+hipError_t launch_layout_mx<false, false>(const GemmParams& p, int fa, int fb, hipStream_t s) {
   return by_formats<DirectFamily<false, false, true>::template F>(p, fa, fb, s);
 }
 

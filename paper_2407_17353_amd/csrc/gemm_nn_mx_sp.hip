@@ -6,7 +6,7 @@
 namespace scalify {
 
 template <>
-hipError_t launch_layout_mx_sp<false, false>(const GemmParams& p, int fa, int fb, int, hipStream_t s) {
+hipError_t launch_layout_mx_sp<false, false>(const GemmParams& p, int fa, int fb, hipStream_t s) {
   return by_formats<SpFamily<false, false, true>::template F>(p, fa, fb, s);
 }
 

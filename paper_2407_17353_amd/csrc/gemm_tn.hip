@@ -5,8 +5,8 @@
 namespace scalify {
 
 template <>
-hipError_t launch_layout<true, false, false>(const GemmParams& p, int fa, int fb, int, hipStream_t s) {
-  return by_formats<PlainFamily<true, false, false>::template F>(p, fa, fb, s);
+hipError_t launch_layout<true, false>(const GemmParams& p, int fa, int fb, hipStream_t s) {
+  return by_formats<PlainFamily<true, false>::template F>(p, fa, fb, s);
 }
 
 }  // namespace scalify

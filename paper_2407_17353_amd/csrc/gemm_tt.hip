@@ -5,8 +5,8 @@
 namespace scalify {
 
 template <>
-hipError_t launch_layout<true, true, false>(const GemmParams& p, int fa, int fb, int, hipStream_t s) {
-  return by_formats<PlainFamily<true, true, false>::template F>(p, fa, fb, s);
+hipError_t launch_layout<true, true>(const GemmParams& p, int fa, int fb, hipStream_t s) {
+  return by_formats<PlainFamily<true, true>::template F>(p, fa, fb, s);
 }
 
 }  // namespace scalify

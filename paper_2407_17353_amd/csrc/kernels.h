@@ -5,18 +5,17 @@
 
 namespace scalify {
 
-// Workspace header, in 32-bit words at the start of every workspace:
-//   [0] amax as fp32 bits (atomic max target; zeroed by the prologue)
+// Workspace header, in 32-bit words at the start of every workspace
+// (call_header.h: its life within a matmul call; stat_header.h: of the
+// rescale and the LayerNorm backward, words 0, 1, 32 and 33):
+//   [0] amax as fp32 bits (atomic max target)
 //   [1] e_w, the scale exponent of the pre-cast value w (the exponent sum of
-//       the input scales, or the scaled-add exponent with a residual):
-//       snapshot taken by the prologue, so that an output scale aliasing an
-//       input scale cannot race
-//   [2] direct cast (delayed rescale, or none): its shift, data' = w * 2^-shift
-//   [3] fused residual add: shift of acc into w's scale (e_a + e_b - e_w)
-//   [4] fused residual add: shift of the residual (q - e_w)
-//   [5] single pass: workgroups arrived at the grid barrier (zeroed by the prologue)
-//   [6] single pass: barrier state, 0 running, 1 complete, 2 aborted (zeroed by the prologue)
-//   [7] single pass: workgroups that wrote their held tile after an abort (zeroed by the prologue)
+//       the input scales, or the scaled-add exponent with a residual)
+//   [5] workgroups that have folded their maximum in
+//   [6] single pass: barrier state, 0 running, 1 complete, 2 aborted
+//   [7] single pass: workgroups that wrote their held tile after an abort
+//   [32] and [33] the call's tag while the header is in use
+//   [34] single pass: the barrier's decision, polled
 constexpr size_t kHeaderBytes = 256;
 
 // Activation of the fused epilogue (values of scalify_activation).
@@ -36,6 +35,15 @@ struct GemmParams {
   int M, N, K;
   int tiles_m, tiles_n;
   int e_c;        // matmul scale rule exponent
+  int e_cc;       // exponent offset of the statistic: e_c, or 0 with a residual
+  const float* s0;       // scales of a, b and the residual (NULL = 1)
+  const float* s1;
+  const float* s_res;
+  const float* amax_in;  // delayed rescale: the statistic of an earlier call
+  uint64_t tag;          // of this call (call_header.h)
+  int uses_header;       // the call needs the header's words
+  int counted;           // direct cast: the last workgroup writes scale and statistic
+  int residual;          // scaled add of a residual (whose data may be empty)
   int sat;
   uint32_t* hdr;  // workspace header
   void* inter;    // pre-cast intermediate [M][ldw] (EPI_INTER16: u16, EPI_INTER32: f32)
@@ -44,7 +52,7 @@ struct GemmParams {
   void* out;       // EPI_DIRECT: output codes [M][ldc] of format out_fmt
   int64_t ldc;
   int out_fmt;
-  // Fused epilogue (FUSE kernels only): residual codes [M][ldr] (ldr = 0:
+  // Fused epilogue: residual codes [M][ldr] (ldr = 0:
   // one row for every row) of format res_fmt or NULL, activation, and the
   // optional export of the pre-cast value w [M][N].
   const void* res;
@@ -52,7 +60,7 @@ struct GemmParams {
   int res_fmt;
   int act;
   float* pre_out;
-  // Channel scales (FUSE kernels only): powers of two per output row
+  // Channel scales: powers of two per output row
   // (ch_a [M]) and per output column (ch_b [N]) multiplied into the
   // accumulator with the power-of-two product of the epilogue; NULL = 1.
   const float* ch_a;
@@ -71,7 +79,7 @@ struct GemmParams {
   // the output scale and statistic it writes, and the barrier's wait budget
   // in ticks of the 100 MHz real-time counter.
   int grid;
-  int epi;  // Epi of the launch (set by launch_gemm)
+  int epi;  // Epi of the launch
   int single_pass;
   int target;
   float* out_scale;
@@ -88,40 +96,28 @@ int gemm4_grid(int tiles);
 hipError_t launch_mx_pack(const uint8_t* src, int rows, int K, int ld, uint8_t* dst,
                           hipStream_t s);
 
-// fuse: launch the kernels with the fused residual add / activation / pre_out
-// epilogue (the plain kernels otherwise).
-hipError_t launch_gemm(const GemmParams& p, bool a_mn, bool b_kc, int fa, int fb, int epi,
-                       bool fuse, hipStream_t s);
+hipError_t launch_gemm(const GemmParams& p, bool a_mn, bool b_kc, int fa, int fb, hipStream_t s);
+
+// The 256 x 256 kernel with the fused epilogue (one workgroup per tile).
+hipError_t launch_fused_gemm(const GemmParams& p, bool a_mn, bool b_kc, int fa, int fb,
+                             hipStream_t s);
 
 // Header of a rescale without a statistic: hdr[0] = 0, hdr[1] = exponent(s0)
 // (NULL = scale 1).
 hipError_t launch_prologue(uint32_t* hdr, const float* s0, hipStream_t s);
 
-// Prologue of the matmul: hdr[0] = hdr[5] = hdr[6] = hdr[7] = 0 and hdr[1] =
-// e_w, the scale exponent of the pre-cast value: e_a + e_b, or with a
-// residual of scale 2^q the scaled add exponent max(e_a + e_b + e_c, q)
-// (sqrt(s_p^2 + s_r^2) rounded down), with hdr[3] = e_a + e_b - e_w and
-// hdr[4] = q - e_w. Direct cast (output scale known before the GEMM): from
-// the statistic *amax_in of an earlier call (delayed rescale; e_r =
-// floor(log2 amax_in) - target, 0 when amax_in is 0, Inf or NaN) or with
-// e_r = 0 (no rescale, amax_in NULL): writes *out_scale = 2^e_out, e_out =
-// clamp(e_w + e_cc + e_r), and hdr[2] = e_out - e_w, where e_cc = e_c
-// without a residual and 0 with one.
-struct MatmulPrologue {
+// A matmul with no output elements: output scale and statistic alone.
+struct EmptyMatmul {
   const float* s0;
   const float* s1;
-  const float* s_res;  // residual scale (NULL = 1)
-  int residual;        // 1: scaled add of a residual
-  int e_c;
-  int direct;
-  const float* amax_in;
+  const float* s_res;    // residual scale (NULL = 1)
+  int residual, e_c;
+  const float* amax_in;  // delayed rescale, else NULL
   int target;
   float* out_scale;
+  float* amax_out;       // or NULL
 };
-hipError_t launch_matmul_prologue(uint32_t* hdr, const MatmulPrologue& q, hipStream_t s);
-
-// *amax_out = amax recorded in hdr[0] (max |w|) times 2^-e_cc.
-hipError_t launch_finalize_amax(const uint32_t* hdr, int e_c, float* amax_out, hipStream_t s);
+hipError_t launch_empty_matmul(const EmptyMatmul& q, hipStream_t s);
 
 // Cast of the GEMM intermediate [M][ldw] to out [M][ldc]; computes the
 // rescale exponent from hdr and writes *out_scale (and *amax_out).
@@ -132,7 +128,7 @@ struct EpilogueParams {
   int64_t ldc;
   int M, N;
   int e_c, target, sat, mode;
-  const uint32_t* hdr;
+  uint32_t* hdr;  // (its tag is taken out: the call is done with the header)
   float* out_scale;
   float* amax_out;
 };

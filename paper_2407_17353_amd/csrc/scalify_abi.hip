@@ -13,6 +13,8 @@
 #include "../../include/scalify.h"
 #include "kernels.h"
 #include "layernorm.h"
+#include "mid_gemm.h"
+#include "wave_gemm.h"
 
 using namespace scalify;
 
@@ -68,7 +70,57 @@ bool single_pass_choice(int64_t tiles, int grid) {
   return tiles <= grid;
 }
 
-// Tag of a call (stat_header.h): never zero, different for every call of the
+// The GEMM kernel of a call and its output tile.
+enum GemmKind { GEMM_BIG, GEMM_FUSED, GEMM_MID, GEMM_WAVE };
+struct GemmChoice {
+  GemmKind kind;
+  int tm, tn;
+  int64_t tiles;
+  MidTile mid;
+  int resident;  // workgroups that a CU holds
+};
+
+// The rule, on the counts of tiles that each kernel would have (times in us,
+// AMAX, [M][K] x [K][N], 256 CUs, the two kernels in the order named):
+// - Up to one 16/32/64 x 64 tile per CU: the wave kernel, whose 4 waves split
+//   K. 64x4096x4096 (64 tiles) against 128 x 128 tiles 16.1 / 25.4,
+//   256x4096x4096 (256) 22.2 / 24.5, 256x4096x8192 without rescale 25 / 47;
+//   with one more tile per CU it loses, 512x4096x1024 (512) 23.2 / 15.7.
+//   Block scales, which the 128-row kernel does not have, take it up to two
+//   tiles per CU, against 256 x 256 tiles: 512x4096x4096 34.5 / 53.6, but
+//   1024x4096x1024 (1024) 35.3 / 25.0.
+// - Up to one 128 x 256 tile per CU: the 128-row kernel, a 256 x 256 grid
+//   leaving half the chip idle. 128 x 128 tiles, two workgroups to a CU, while
+//   K is short: 1024x4096x1024 19.4 against 20.9 of 128 x 256 and 23.4 of
+//   256 x 256 tiles. A deeper ring (one workgroup to a CU) or the larger tile
+//   for long K: 2048x2048x8192 56.6 / 51.9, 2048x4096x8192 72.3 / 63.7
+//   (256 x 256: 87.4).
+// - Else 256 x 256 tiles; with a fused epilogue, which that kernel has only in
+//   its slower 8-wave form, 128 x 128 tiles where these fill their rounds of
+//   512 that much better than 256 x 256 tiles fill rounds of 256 (a round of
+//   them takes 9/16 of the other's time): bias and GELU 3001x8192x2048 (3 and
+//   2 rounds) 90.5 against 102.0, 4096x8192x2048 (4 and 2) 118 / 112,
+//   8192x8192x2048 304 / 243. (Without one: 3001x8192x2048 71.7 / 65.4.)
+// The choice depends on sizes alone, not on the mode: all ways of a call sum
+// in one order.
+GemmChoice gemm_choice(int64_t M, int64_t N, int64_t K, int cus, bool fused, bool mx) {
+  auto make = [&](GemmKind k, int tm, int tn, MidTile t = MID_256) {
+    return GemmChoice{k, tm, tn, ((M + tm - 1) / tm) * ((N + tn - 1) / tn), t, t == MID_128_PAIR ? 2 : 1};
+  };
+  const GemmChoice big = make(fused ? GEMM_FUSED : GEMM_BIG, 256, 256);
+  const GemmChoice wave = make(GEMM_WAVE, wave_tile_rows(M), kWaveTN);
+  const GemmChoice mid8 = make(GEMM_MID, kMidTM, 256, MID_256);
+  const GemmChoice mid4 = make(GEMM_MID, kMidTM, 128, MID_128);
+  const GemmChoice pair = make(GEMM_MID, kMidTM, 128, MID_128_PAIR);
+  if (mx) return wave.tiles <= 2 * cus ? wave : big;
+  if (wave.tiles <= cus) return wave;
+  if (mid8.tiles <= cus) return K < 4096 ? pair : mid4.tiles <= cus ? mid4 : mid8;
+  if (!fused) return big;
+  const int64_t big_rounds = (big.tiles + cus - 1) / cus, pair_rounds = (pair.tiles + 2 * cus - 1) / (2 * cus);
+  return 9 * pair_rounds < 16 * big_rounds ? pair : big;
+}
+
+// Tag of a call (call_header.h): never zero, different for every call of the
 // process, and not what a workspace holds by chance.
 uint64_t next_tag() {
   static std::atomic<uint64_t> next{[] {
@@ -332,28 +384,44 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
   const int epi = !amax_mode ? EPI_DIRECT
                              : ((opts->out_dtype == SCALIFY_F16 || fused || mx) ? EPI_INTER32
                                                                                  : EPI_INTER16);
-  const bool tn_mx = mx && a->trans != 0 && b->trans == 0;  // 8-wave kernel
-  // (the 4-wave block-scaled kernel casts only in the single pass)
+  // (256 x 256 kernel without the single pass: fused, or block scales of
+  // A [K][M] with B [K][N])
+  const bool tn_mx = mx && a->trans != 0 && b->trans == 0;
   const bool persistent = persistent_enabled();
-  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  const int grid = persistent ? gemm4_grid((int)tiles) : (int)tiles;
+  const int cus = gemm4_grid(1 << 30);
+  const GemmChoice gc = gemm_choice(M, N, K, cus, fused, mx);
+  int grid = (int)gc.tiles;
+  if (persistent && gc.kind != GEMM_FUSED && grid > gc.resident * cus) grid = gc.resident * cus;
+  // Single pass where each workgroup can hold its tiles: the wave kernel by
+  // its choice always, the others with one tile each. (Forced, the 256 x 256
+  // kernel holds its last tile and passes the others through the intermediate.)
   const bool single_pass =
-      amax_mode && !fused && !tn_mx && persistent && single_pass_choice(tiles, grid);
+      amax_mode && persistent && gc.kind != GEMM_FUSED &&
+      (gc.kind == GEMM_BIG ? !tn_mx && single_pass_choice(gc.tiles, grid)
+                           : (gc.kind == GEMM_WAVE || gc.tiles <= grid) && single_pass_choice(0, 0));
   // Exponent offset of the statistic: the matmul data is acc * 2^-e_c; with
   // a residual the statistic is taken over w itself.
   const int e_cc = res ? 0 : e_c;
+  hipEvent_t* ev = (hipEvent_t*)opts->events;
+  auto record = [&](int i) {
+    return !ev || !ev[i] || hipEventRecord(ev[i], s) == hipSuccess;
+  };
 
-  MatmulPrologue pq = {};
-  pq.s0 = a->scale;
-  pq.s1 = b->scale;
-  pq.s_res = res ? res->scale : nullptr;
-  pq.residual = res ? 1 : 0;
-  pq.e_c = e_c;
-  pq.direct = epi == EPI_DIRECT ? 1 : 0;
-  pq.amax_in = delayed ? opts->amax_in : nullptr;
-  pq.target = opts->target_log2;
-  pq.out_scale = out->scale;
-  if (launch_matmul_prologue(hdr, pq, s) != hipSuccess) return SCALIFY_ERR_HIP;
+  if (M == 0 || N == 0) {
+    EmptyMatmul q = {};
+    q.s0 = a->scale;
+    q.s1 = b->scale;
+    q.s_res = res ? res->scale : nullptr;
+    q.residual = res ? 1 : 0;
+    q.e_c = e_c;
+    q.amax_in = delayed ? opts->amax_in : nullptr;
+    q.target = opts->target_log2;
+    q.out_scale = out->scale;
+    q.amax_out = opts->amax_out;
+    if (!record(0) || launch_empty_matmul(q, s) != hipSuccess || !record(1) || !record(2))
+      return SCALIFY_ERR_HIP;
+    return SCALIFY_OK;
+  }
 
   GemmParams p = {};
   p.a = (const uint8_t*)a->data;
@@ -363,11 +431,24 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
   p.M = (int)M;
   p.N = (int)N;
   p.K = (int)K;
-  p.tiles_m = (int)((M + 255) / 256);
-  p.tiles_n = (int)((N + 255) / 256);
+  p.tiles_m = (int)((M + gc.tm - 1) / gc.tm);
+  p.tiles_n = (int)((N + gc.tn - 1) / gc.tn);
   p.a_bytes = (uint32_t)(stored_rows(a) * a->ld);
   p.b_bytes = (uint32_t)(stored_rows(b) * b->ld);
   p.e_c = e_c;
+  p.e_cc = e_cc;
+  p.s0 = a->scale;
+  p.s1 = b->scale;
+  p.s_res = res ? res->scale : nullptr;
+  p.amax_in = delayed ? opts->amax_in : nullptr;
+  p.residual = res ? 1 : 0;
+  // The direct cast needs the header only for a statistic, or where the
+  // output scale shares memory with what other workgroups still read.
+  const float* o = out->scale;
+  p.counted = epi == EPI_DIRECT &&
+              (opts->amax_out || o == p.s0 || o == p.s1 || o == p.s_res || o == p.amax_in);
+  p.uses_header = epi != EPI_DIRECT || p.counted;
+  p.tag = p.uses_header ? next_tag() : 0;
   p.sat = opts->saturate != 0;
   p.hdr = hdr;
   p.inter = (uint8_t*)workspace + kHeaderBytes;
@@ -376,7 +457,7 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
   p.out = out->data;
   p.ldc = out->ld;
   p.out_fmt = opts->out_dtype;
-  p.res = res && M > 0 && N > 0 ? res->data : nullptr;
+  p.res = res ? res->data : nullptr;
   p.ldr = res ? res->ld : 0;
   p.res_fmt = res ? res->dtype : 0;
   p.act = opts->activation;
@@ -391,40 +472,21 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
   p.mx_a_bytes = (uint32_t)mx_a_bytes;
   p.mx_b_bytes = (uint32_t)mx_b_bytes;
   p.grid = grid;
+  p.epi = epi;
   p.single_pass = single_pass ? 1 : 0;
   p.target = opts->target_log2;
   p.out_scale = out->scale;
   p.amax_out = opts->amax_out;
   p.spin_ticks = spin_ticks(K);
-  hipEvent_t* ev = (hipEvent_t*)opts->events;
-  if (ev && ev[0] && hipEventRecord(ev[0], s) != hipSuccess) return SCALIFY_ERR_HIP;
-  if (M > 0 && N > 0) {
-    if (launch_gemm(p, a->trans != 0, b->trans != 0, a->dtype, b->dtype, epi, fused, s) !=
-        hipSuccess)
-      return SCALIFY_ERR_HIP;
-  }
-  if (ev && ev[1] && hipEventRecord(ev[1], s) != hipSuccess) return SCALIFY_ERR_HIP;
-  if (epi == EPI_DIRECT) {
-    // The statistic this call records (for the next one, when delayed).
-    if (opts->amax_out && launch_finalize_amax(hdr, e_cc, opts->amax_out, s) != hipSuccess)
-      return SCALIFY_ERR_HIP;
-  } else if (single_pass) {
-    // The GEMM has cast the output and written its scale and statistic; with
-    // nothing to compute (an empty output) they are written here.
-    if (M == 0 || N == 0) {
-      EpilogueParams q = {};
-      q.M = 0;
-      q.N = (int)N;
-      q.e_c = e_cc;
-      q.target = opts->target_log2;
-      q.mode = 1;
-      q.hdr = hdr;
-      q.out_scale = out->scale;
-      q.amax_out = opts->amax_out;
-      if (launch_epilogue_cast(q, epi == EPI_INTER32, opts->out_dtype, s) != hipSuccess)
-        return SCALIFY_ERR_HIP;
-    }
-  } else {
+  const bool ta = a->trans != 0, tb = b->trans != 0;
+  if (!record(0)) return SCALIFY_ERR_HIP;
+  if ((gc.kind == GEMM_WAVE  ? launch_wave_gemm(p, ta, tb, a->dtype, b->dtype, s)
+       : gc.kind == GEMM_MID ? launch_mid_gemm(p, ta, tb, a->dtype, b->dtype, gc.mid, s)
+       : gc.kind == GEMM_FUSED ? launch_fused_gemm(p, ta, tb, a->dtype, b->dtype, s)
+                             : launch_gemm(p, ta, tb, a->dtype, b->dtype, s)) != hipSuccess)
+    return SCALIFY_ERR_HIP;
+  if (!record(1)) return SCALIFY_ERR_HIP;
+  if (epi != EPI_DIRECT && !single_pass) {
     // Second pass of the two-kernel dynamic rescale: global amax -> rescale
     // exponent -> output scale, and the cast of the intermediate.
     EpilogueParams q = {};
@@ -432,7 +494,7 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
     q.ldw = p.ldw;
     q.out = out->data;
     q.ldc = out->ld;
-    q.M = N > 0 ? (int)M : 0;
+    q.M = (int)M;
     q.N = (int)N;
     q.e_c = e_cc;
     q.target = opts->target_log2;
@@ -444,8 +506,7 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
     if (launch_epilogue_cast(q, epi == EPI_INTER32, opts->out_dtype, s) != hipSuccess)
       return SCALIFY_ERR_HIP;
   }
-  if (ev && ev[2] && hipEventRecord(ev[2], s) != hipSuccess) return SCALIFY_ERR_HIP;
-  return SCALIFY_OK;
+  return record(2) ? SCALIFY_OK : SCALIFY_ERR_HIP;
 }
 
 scalify_status scalify_matmul_noalloc(const scalify_scaled_array* a,
