@@ -339,8 +339,8 @@ scalify_status scalify_set_scaling(const scalify_scaled_array* in, scalify_scale
  * may be the very same matrix as x (same data, element size and ld) but must
  * not otherwise overlap it. pre_out: optional device fp32 [R][D] receiving y
  * before the cast (validation). The statistics are fp32 sums in a fixed
- * order: reruns are bit-identical. Rows of 2049 .. 4096 FP16 / FP8 elements
- * are read from HBM once (the backward's statistics too);
+ * order: reruns are bit-identical. Rows are read from HBM once (by the
+ * backward's statistics too);
  * SCALIFY_LN_SINGLE_READ=0 (read at each call) selects the multi-pass
  * kernels instead, with the same results bit for bit. */
 scalify_status scalify_layernorm_fwd(const scalify_scaled_array* x, const float* gamma,
