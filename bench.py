@@ -2,7 +2,7 @@
 """Benchmark of the scaled-FP8 matmul with fused dynamic rescale and cast.
 
 One step = one scalify_matmul call on the headline workload: M = N = K = 8192,
-E4M3 x E4M3 -> E4M3 with the amax rescale (prologue + fused GEMM/amax +
+E4M3 x E4M3 -> E4M3 with the amax rescale (fused GEMM/amax +
 epilogue cast), inputs already resident in HBM. Prints ONE JSON line with
 the whole-call throughput (TFLOP/s), the roofline of the dominant kernel
 (the fused GEMM, timed live with HIP events recorded by the library on its
@@ -434,7 +434,7 @@ def main():
                    "out_fmt": "e4m3", "layout": "A [M][K], B [K][N]",
                    "scales_log2": [case.a_scale_log2, case.b_scale_log2]},
         "pct_of_peak": round(100.0 * value / PEAK_FP8_TFLOPS, 2),
-        # whole call (prologue + GEMM + cast, every launch gap) against the
+        # whole call (GEMM + cast, every launch gap) against the
         # dense FP8 peak; roofline.frac below is the GEMM kernel alone
         "frac_call": round(value / PEAK_FP8_TFLOPS, 4),
         "gemm_kernel_us": round(res["gemm_ms"] * 1e3, 2),
