@@ -2,25 +2,21 @@
 // workgroup derives from the scales, and the header's life within one call
 // without a kernel that clears it first.
 //
-// The workspace arrives with any contents. Workgroup 0 clears the header's
-// words when it starts and then publishes the call's tag (a 64-bit number
-// that the host draws anew for every call); a workgroup uses the header, at
-// its end, only once it has seen the tag. Whoever ends the call's use of the
-// header takes the tag out again, so that a replay of the same launch (a
-// captured graph carries the same tag every time) starts like the first one:
+// Workgroup 0 claims, clears and publishes the header once its first loads
+// are under way, so that the others, which use it at their end, find it ready;
+// a workgroup that comes there before it has, does so in its place
+// (header_tag.h: nothing depends on the order of dispatch). Whoever ends the
+// call's use of the header takes the tag out again:
 //   single pass: the first workgroup, once every workgroup has arrived (or,
 //     after an abort, the last one to have written its tiles);
 //   direct cast with a statistic: the last workgroup to arrive;
 //   GEMM + cast kernel: the cast kernel.
-// Workgroup 0 is never dispatched after the others of its launch and clears
-// the header first thing, so the wait for the tag ends. (A kernel that
-// clears the header ahead of the GEMM cost 4.7 us of every call; the amax
-// write-back of the direct cast another 4.7 us.)
 //
 // Output scale and statistic are written only after every workgroup has
 // arrived, so they may share memory with an input scale or with amax_in.
 #pragma once
 #include "codec.h"
+#include "header_tag.h"
 #include "kernels.h"
 
 namespace scalify {
@@ -99,7 +95,7 @@ __device__ __forceinline__ uint64_t* hdr_tag(const GemmParams& p) {
   return (uint64_t*)(p.hdr + kHdrTag);
 }
 
-// Workgroup 0, one thread, before its first loads: clear the header ...
+// The header's words as a call starts with them.
 __device__ __forceinline__ void header_clear(const GemmParams& p, int e_w) {
   hdr_store(p.hdr, 0u);
   hdr_store(p.hdr + 1, (uint32_t)e_w);
@@ -108,21 +104,29 @@ __device__ __forceinline__ void header_clear(const GemmParams& p, int e_w) {
   hdr_store(p.hdr + kHdrGo, (uint32_t)SP_RUNNING);
   hdr_store(p.hdr + kHdrWritten, 0u);
 }
-// ... and, the same thread, once those stores are done (after a wait that
-// covers them: vector memory completes in issue order): publish the tag.
-__device__ __forceinline__ void header_publish(const GemmParams& p) {
-  __hip_atomic_store(hdr_tag(p), p.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Workgroup 0, one thread, with its first loads under way (the claim waits for
+// them): whether it has claimed the header; its words are then on their way
+// and header_publish follows, the same thread, after a wait that covers them
+// (vector memory completes in issue order).
+__device__ __forceinline__ bool header_begin(const GemmParams& p, const RawScales& r) {
+  if (!tag_claim(hdr_tag(p), p.tag)) return false;
+  header_clear(p, call_exponents(p, r).e_w);
+  return true;
 }
-__device__ __forceinline__ void header_retire(const GemmParams& p) {
-  __hip_atomic_store(hdr_tag(p), (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void header_publish(const GemmParams& p) { tag_store(hdr_tag(p), p.tag); }
+// Both, where the kernel has nothing to do in between.
+__device__ __forceinline__ void header_open(const GemmParams& p, const RawScales& r) {
+  if (!header_begin(p, r)) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  header_publish(p);
 }
-// One thread of a workgroup, before its first use of the header. (The poll
-// count, seconds of polling, is there only so that every wait ends.)
-__device__ __forceinline__ void header_await(const GemmParams& p) {
-  for (int it = 0; it < (1 << 22); ++it) {
-    if (__hip_atomic_load(hdr_tag(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.tag) return;
-    __builtin_amdgcn_s_sleep(2);
-  }
+__device__ __forceinline__ void header_retire(const GemmParams& p) { tag_store(hdr_tag(p), 0); }
+// One thread of a workgroup, before its first use of the header.
+__device__ __forceinline__ void header_await(const GemmParams& p, int e_w) {
+  tag_await(hdr_tag(p), p.tag, [&] {
+    header_clear(p, e_w);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  });
 }
 
 // Fold the workgroup's statistic and count its arrival: returns how many have
@@ -137,22 +141,23 @@ __device__ __forceinline__ uint32_t header_arrive(const GemmParams& p, float wma
 // End of a workgroup of the direct cast, one thread: with a statistic to
 // report (or an output scale that shares memory with an input), the last
 // workgroup to arrive writes both; else workgroup 0 writes the scale.
-__device__ __forceinline__ void direct_finish(const GemmParams& p, float wmax, int G, int e_out) {
+__device__ __forceinline__ void direct_finish(const GemmParams& p, float wmax, int G,
+                                              const CallExponents& x) {
   if (p.counted) {
-    header_await(p);
+    header_await(p, x.e_w);
     if (header_arrive(p, wmax) != (uint32_t)G) return;
     if (p.amax_out)
       *p.amax_out = __uint_as_float(hdr_load(p.hdr)) * pow2_float(-p.e_cc);
     header_retire(p);
-    *p.out_scale = pow2_float(e_out);
+    *p.out_scale = pow2_float(x.e_out);
   } else if (blockIdx.x == 0) {
-    *p.out_scale = pow2_float(e_out);
+    *p.out_scale = pow2_float(x.e_out);
   }
 }
 
 // End of a workgroup of the GEMM that leaves the cast to a kernel of its own.
-__device__ __forceinline__ void pair_finish(const GemmParams& p, float wmax) {
-  header_await(p);
+__device__ __forceinline__ void pair_finish(const GemmParams& p, float wmax, int e_w) {
+  header_await(p, e_w);
   atomicMax(p.hdr, __float_as_uint(wmax));
 }
 
@@ -172,8 +177,9 @@ __device__ __forceinline__ uint32_t grid_decide(const GemmParams& p, uint32_t de
   return decision;
 }
 
-__device__ __forceinline__ uint32_t grid_arrive(const GemmParams& p, float wmax, int G) {
-  header_await(p);
+__device__ __forceinline__ uint32_t grid_arrive(const GemmParams& p, float wmax, int G,
+                                                int e_w) {
+  header_await(p, e_w);
   if (header_arrive(p, wmax) != (uint32_t)G) return SP_RUNNING;
   return grid_decide(p, SP_COMPLETE);
 }

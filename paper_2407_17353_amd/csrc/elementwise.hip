@@ -216,10 +216,7 @@ __global__ __launch_bounds__(EW_THREADS) void amax_kernel(const void* in, int64_
                                                            uint32_t* hdr, uint64_t tag) {
   using L = BlockLayout<F>;
   __shared__ uint32_t red[EW_THREADS / 64];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    stat_clear(hdr, in_scale, nullptr);
-    stat_publish(hdr, tag);
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) stat_open(hdr, tag, in_scale, nullptr);
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * (EW_THREADS / 64) + (threadIdx.x >> 6);
   const int64_t waves = (int64_t)gridDim.x * (EW_THREADS / 64);
@@ -260,7 +257,7 @@ __global__ __launch_bounds__(EW_THREADS) void amax_kernel(const void* in, int64_
     two_blocks();
     const float m = block_max();
     if (threadIdx.x == 0) {
-      stat_await(hdr, tag);
+      stat_await(hdr, tag, in_scale, nullptr);
       known = fmaxf(stat_fold(hdr, m), m);
     }
   }
@@ -278,7 +275,7 @@ __global__ __launch_bounds__(EW_THREADS) void amax_kernel(const void* in, int64_
       kmax = max(kmax, magnitude_key<F>(load1<F>(in, e)));
   const float m = block_max();
   if (threadIdx.x == 0 && m > known) {
-    stat_await(hdr, tag);
+    stat_await(hdr, tag, in_scale, nullptr);
     stat_fold(hdr, m);
   }
 }

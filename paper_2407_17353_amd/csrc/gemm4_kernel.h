@@ -165,8 +165,6 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
   const v4i ra = make_rsrc(p.a, p.a_bytes);
   const v4i rb = make_rsrc(p.b, p.b_bytes);
   const RawScales raw_scales = load_scales(p);
-  if (blockIdx.x == 0 && tid == 0 && p.uses_header)
-    header_clear(p, call_exponents(p, raw_scales).e_w);
 
   // Per-load parts of the load offsets, per lane (load q of this wave's share
   // of a tile: block blk = wave * BPW + q): KC rows along M/N, MC rows along
@@ -599,9 +597,9 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
   issue_scale_half(1, false);
   issue_scale_half(1, true);
   advance();
+  const bool opens = blockIdx.x == 0 && tid == 0 && p.uses_header && header_begin(p, raw_scales);
   static_for<0, MI * NI>([&](auto I) { AccTile<decltype(I)::value>::zero(); });
   wait_vmcnt<LOADS_PER_STEP + (MX ? 2 : 0)>();
-  if (blockIdx.x == 0 && tid == 0 && p.uses_header) header_publish(p);
   __syncthreads();
   if (KT_full == 0 && (krem & 15)) zero_tail(sA0, sB0);
 #pragma unroll
@@ -615,6 +613,10 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
     sb[0][1] = scale_word(0, 1, wn / 64 + 1);
   }
   mfma_drain();
+  if (opens) {
+    wait_vmcnt<0>();  // (its words; the loads before them have landed)
+    header_publish(p);
+  }
 
   using P0 = std::integral_constant<int, 0>;
   using P1 = std::integral_constant<int, 1>;
@@ -685,9 +687,9 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
     if (tid == 0) {
       const float wmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
       if constexpr (EPI == EPI_DIRECT)
-        direct_finish(p, wmax, G, ex.e_out);
+        direct_finish(p, wmax, G, ex);
       else
-        pair_finish(p, wmax);
+        pair_finish(p, wmax, e_w);
     }
     return;
   } else {
@@ -827,7 +829,7 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
     const bool own = ntiles > 1;
     uint32_t arrived = SP_RUNNING;
     if (tid == 0)
-      arrived = grid_arrive(p, fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), G);
+      arrived = grid_arrive(p, fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), G, e_w);
     // the first batch of the earlier tiles in flight during the wait (issued
     // after the arrival, which waits for every load of its wave)
     if (own) {

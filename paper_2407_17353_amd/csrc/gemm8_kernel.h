@@ -184,7 +184,6 @@ __global__ __launch_bounds__(512, 1) void gemm8_kernel(GemmParams p) {
   tile_origin(blockIdx.x, p.tiles_m, p.tiles_n, m0, n0);
   const RawScales raw_scales = load_scales(p);
   const bool first = blockIdx.x == 0 && tid == 0 && p.uses_header;
-  if (first) header_clear(p, call_exponents(p, raw_scales).e_w);
 
   const int M = p.M, N = p.N, K = p.K;
   const int KT = (K + BK - 1) / BK;
@@ -346,11 +345,13 @@ __global__ __launch_bounds__(512, 1) void gemm8_kernel(GemmParams p) {
       if (KT > 1) {
         issue_all(1, sA1, sB1);
         issue_scales(1, 1);
+      }
+      const bool opens = first && header_begin(p, raw_scales);
+      if (KT > 1) {
         wait_vmcnt<LOADS_PER_STEP + (MX ? 1 : 0)>();  // step 1's loads may be in flight
       } else {
         wait_vmcnt<0>();
       }
-      if (first) header_publish(p);
       __syncthreads();
       if (KT_full == 0 && (krem & 15)) zero_tail(sA0, sB0);
 #pragma unroll
@@ -362,9 +363,12 @@ __global__ __launch_bounds__(512, 1) void gemm8_kernel(GemmParams p) {
         sb[0] = scale_word(0, 1, wn / 64);
         sb[1] = scale_word(0, 1, wn / 64 + 1);
       }
+      if (opens) {
+        wait_vmcnt<0>();  // (its words; the loads before them have landed)
+        header_publish(p);
+      }
     } else if (first) {
-      wait_vmcnt<0>();
-      header_publish(p);
+      header_open(p, raw_scales);
     }
     int kt = 0;
     for (; kt + 2 < KT; ++kt) step(T_{}, T_{}, kt);
@@ -513,8 +517,8 @@ __global__ __launch_bounds__(512, 1) void gemm8_kernel(GemmParams p) {
   if (tid == 0) {
     float wmax = red[0];
     for (int w = 1; w < WAVES; ++w) wmax = fmaxf(wmax, red[w]);
-    if (EPI == EPI_DIRECT) direct_finish(p, wmax, gridDim.x, ex.e_out);
-    else pair_finish(p, wmax);
+    if (EPI == EPI_DIRECT) direct_finish(p, wmax, gridDim.x, ex);
+    else pair_finish(p, wmax, ex.e_w);
   }
 }
 

@@ -105,10 +105,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_stats_kernel(LnParams p) {
   // in the single-read and multi-pass kernels, so both round alike)
 #pragma clang fp contract(off)
   __shared__ float wmax[4];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    stat_clear(p.hdr, p.s_dy, p.s_x);
-    stat_publish(p.hdr, p.tag);
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) stat_open(p.hdr, p.tag, p.s_dy, p.s_x);
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int nch = (p.D + 15) / 16;
@@ -164,7 +161,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_stats_kernel(LnParams p) {
   if (lane == 0) wmax[wave] = lmax;
   __syncthreads();
   if (threadIdx.x == 0) {
-    stat_await(p.hdr, p.tag);
+    stat_await(p.hdr, p.tag, p.s_dy, p.s_x);
     stat_fold(p.hdr, fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])));
   }
 }

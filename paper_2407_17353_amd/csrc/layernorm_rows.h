@@ -153,8 +153,6 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_rows_kernel(LnParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = wave / WPR, part = wave % WPR;
   const RowChunks<WPR, FULL> ch(p.D, part, lane);
-  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
-  if (first) stat_clear(p.hdr, p.s_dy, p.s_x);
   float4* rowstats = (float4*)p.partial;
   const int64_t stride = (int64_t)gridDim.x * RPW;
   uint32_t wx[2][ln_chunk_words<XF>()], wd[2][ln_chunk_words<DYF>()];
@@ -163,7 +161,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_rows_kernel(LnParams p) {
   load_row<DYF>(p.dy, (r0 + slot) * p.lddy, r0 + slot < p.R, ch.n, ch.valid, wd);
   float gam[2][16];
   load_params<FULL>(p.gamma, 1.0f, ch.n, ch.valid, gam);
-  if (first) stat_publish(p.hdr, p.tag);
+  if (blockIdx.x == 0 && threadIdx.x == 0) stat_open(p.hdr, p.tag, p.s_dy, p.s_x);
   float lmax = 0.0f;
   // (the fold after the first rows: see below)
   float known = -1.0f;
@@ -231,7 +229,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_rows_kernel(LnParams p) {
       early = false;
       const float m = block_max();
       if (threadIdx.x == 0) {
-        stat_await(p.hdr, p.tag);
+        stat_await(p.hdr, p.tag, p.s_dy, p.s_x);
         known = fmaxf(stat_fold(p.hdr, m), m);
       }
     }
@@ -239,7 +237,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_rows_kernel(LnParams p) {
   // amax of |dx|: wave butterfly, then the four waves, then the header
   const float m = block_max();
   if (threadIdx.x == 0 && m > known) {
-    stat_await(p.hdr, p.tag);
+    stat_await(p.hdr, p.tag, p.s_dy, p.s_x);
     stat_fold(p.hdr, m);
   }
 }

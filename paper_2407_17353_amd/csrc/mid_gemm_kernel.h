@@ -125,7 +125,6 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
   const int wm = 64 * (wave >> 1), wn = 16 * NI * (wave & 1);
   const RawScales raw_scales = load_scales(p);
   const bool first = blockIdx.x == 0 && tid == 0 && p.uses_header;
-  if (first) header_clear(p, call_exponents(p, raw_scales).e_w);
   const bool fuse = ge_fused(p);
   float* tile = (float*)lds;
   // this thread's groups of a tile: columns tcol .. + 3 of rows trow + DM j
@@ -203,8 +202,8 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
       begin(decltype(I)::value);
       for (int j = 0; j < LPS; ++j) issue_one(j, decltype(I)::value, lds + decltype(I)::value * STAGE);
     });
+    const bool opens = first && t == 0 && header_begin(p, raw_scales);
     wait_vmcnt<(S - 2) * LPS>();
-    if (first && t == 0) header_publish(p);
     __syncthreads();
     zero_tail(0, lds);
     begin(S - 1);
@@ -218,6 +217,10 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
     });
     wait_lgkmcnt<0>();
     mfma_drain();  // (the zeroing, before the first MFMAs read it)
+    if (opens) {
+      wait_vmcnt<LPS>();  // (its words, before the loads of step S - 1)
+      header_publish(p);
+    }
     __builtin_amdgcn_sched_barrier(0);
     int st_i = 0;  // stage of step i
     auto step = [&](auto P, int i) {
@@ -277,8 +280,7 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
     wait_vmcnt<0>();  // the zero loads past the last step
     mfma_drain();
   } else {
-    wait_vmcnt<0>();
-    if (first && t == 0) header_publish(p);
+    if (first && t == 0) header_open(p, raw_scales);
   }
   __syncthreads();
 
@@ -337,18 +339,18 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
   const float wmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   const CallExponents ex = call_exponents(p, raw_scales);
   if (p.epi == EPI_DIRECT) {
-    if (tid == 0) direct_finish(p, wmax, G, ex.e_out);
+    if (tid == 0) direct_finish(p, wmax, G, ex);
     return;
   }
   if (!p.single_pass) {
-    if (tid == 0) pair_finish(p, wmax);
+    if (tid == 0) pair_finish(p, wmax, ex.e_w);
     return;
   }
   // Single pass (one tile per workgroup): the tile in LDS is cast with the
   // rescale of the whole output's statistic; after an abort (the grid was not
   // co-resident) every workgroup writes its tile to the intermediate and the
   // last one casts.
-  if (tid == 0) grid_wait(p, grid_arrive(p, wmax, G), sp_word);
+  if (tid == 0) grid_wait(p, grid_arrive(p, wmax, G, ex.e_w), sp_word);
   __syncthreads();
   uint32_t amax_raw = sp_word[1];
   const bool inside = m0 + TM <= M && n0 + TN <= N;

@@ -120,15 +120,15 @@ GemmChoice gemm_choice(int64_t M, int64_t N, int64_t K, int cus, bool fused, boo
   return 9 * pair_rounds < 16 * big_rounds ? pair : big;
 }
 
-// Tag of a call (call_header.h): never zero, different for every call of the
-// process, and not what a workspace holds by chance.
+// Tag of a call (header_tag.h): even and not zero, different for every call of
+// the process, and not what a workspace holds by chance.
 uint64_t next_tag() {
   static std::atomic<uint64_t> next{[] {
     std::random_device rd;
     return ((uint64_t)rd() << 32) ^ rd();
   }()};
   uint64_t t;
-  do t = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+  do t = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed) << 1;
   while (t == 0);
   return t;
 }

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(WV_THREADS, 1) void wave_gemm_kernel(GemmParams p) 
   constexpr int SLOT = ABYTES + BBYTES + (MX ? 512 : 0);
   constexpr int S = MI == 4 ? 2 : 3;                    // slots of a wave's ring
   constexpr int LPS = TM / 8 + TN / 8 + (MX ? 2 : 0);   // loads per step
-  static_assert((S - 1) * LPS < 64, "vmcnt range");
+  static_assert((S - 1) * LPS < 64 && 2 * LPS < 64, "vmcnt range");
   constexpr int RLD = TN + 4;                           // row stride of the partial tiles (floats)
   static_assert(4 * TM * RLD * 4 <= 4 * S * SLOT, "partial tiles fit the ring");
   constexpr int NG = MI;                                // groups of 4 outputs per thread
@@ -175,7 +175,6 @@ __global__ __launch_bounds__(WV_THREADS, 1) void wave_gemm_kernel(GemmParams p) 
 
   const RawScales raw_scales = load_scales(p);
   const bool first = blockIdx.x == 0 && tid == 0 && p.uses_header;
-  if (first) header_clear(p, call_exponents(p, raw_scales).e_w);
   const bool fuse = ge_fused(p);
   const int trow = tid >> 4, tcol = 4 * (tid & 15);     // this thread's groups in a tile
   float lmax = 0.f;
@@ -242,8 +241,8 @@ __global__ __launch_bounds__(WV_THREADS, 1) void wave_gemm_kernel(GemmParams p) 
     if (steps > 0) {
       static_for<0, S>([&](auto I) { issue(decltype(I)::value, mine + decltype(I)::value * SLOT); });
       Frags f[2];
+      bool opens = first && r == 0 && header_begin(p, raw_scales);
       wait_vmcnt<(S - 1) * LPS>();
-      if (first && r == 0) header_publish(p);
       read(f[0], 0, mine);
       wait_lgkmcnt<0>();
       __builtin_amdgcn_sched_barrier(0);
@@ -264,14 +263,18 @@ __global__ __launch_bounds__(WV_THREADS, 1) void wave_gemm_kernel(GemmParams p) 
 #pragma unroll 1
       for (int i = 0;;) {
         step(f[0], f[1], i);
+        if (opens) {
+          wait_vmcnt<2 * LPS>();  // (its words, before the loads of two steps)
+          header_publish(p);
+          opens = false;
+        }
         if (++i >= steps) break;
         step(f[1], f[0], i);
         if (++i >= steps) break;
       }
       wait_vmcnt<0>();  // the zero loads past the last step
     } else {
-      wait_vmcnt<0>();
-      if (first && r == 0) header_publish(p);
+      if (first && r == 0) header_open(p, raw_scales);
     }
     __syncthreads();
 
@@ -323,18 +326,18 @@ __global__ __launch_bounds__(WV_THREADS, 1) void wave_gemm_kernel(GemmParams p) 
   const float wmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   const CallExponents ex = call_exponents(p, raw_scales);
   if (p.epi == EPI_DIRECT) {
-    if (tid == 0) direct_finish(p, wmax, G, ex.e_out);
+    if (tid == 0) direct_finish(p, wmax, G, ex);
     return;
   }
   if (!p.single_pass) {
-    if (tid == 0) pair_finish(p, wmax);
+    if (tid == 0) pair_finish(p, wmax, ex.e_w);
     return;
   }
 
   // Single pass: the held tiles are cast with the rescale of the whole
   // output's statistic. After an abort (the grid was not co-resident) every
   // workgroup writes its tiles to the intermediate and the last one casts.
-  if (tid == 0) grid_wait(p, grid_arrive(p, wmax, G), sp_word);
+  if (tid == 0) grid_wait(p, grid_arrive(p, wmax, G, ex.e_w), sp_word);
   __syncthreads();
   uint32_t amax_raw = sp_word[1];
   // Held tile h (a copy: one body for all of them) and where it lies.
