@@ -5,10 +5,11 @@
 #include <stdint.h>
 
 #include <stdlib.h>
+#include <time.h>
+#include <unistd.h>
 
 #include <atomic>
 #include <mutex>
-#include <random>
 
 #include "../../include/scalify.h"
 #include "kernels.h"
@@ -120,13 +121,23 @@ GemmChoice gemm_choice(int64_t M, int64_t N, int64_t K, int cus, bool fused, boo
   return 9 * pair_rounds < 16 * big_rounds ? pair : big;
 }
 
+// Where the tags of a process start: its clock, number and address layout,
+// mixed (the finalizer of splitmix64, Steele, Lea and Flood 2014). Nothing here
+// can fail: the callers are C.
+uint64_t first_tag() noexcept {
+  timespec t = {};
+  clock_gettime(CLOCK_REALTIME, &t);
+  uint64_t x = (uint64_t)t.tv_sec * 1000000000u + (uint64_t)t.tv_nsec;
+  x ^= ((uint64_t)getpid() << 40) ^ (uint64_t)(uintptr_t)&t;
+  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+  return x ^ (x >> 31);
+}
+
 // Tag of a call (header_tag.h): even and not zero, different for every call of
 // the process, and not what a workspace holds by chance.
 uint64_t next_tag() {
-  static std::atomic<uint64_t> next{[] {
-    std::random_device rd;
-    return ((uint64_t)rd() << 32) ^ rd();
-  }()};
+  static std::atomic<uint64_t> next{first_tag()};
   uint64_t t;
   do t = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed) << 1;
   while (t == 0);

@@ -5,6 +5,7 @@ any launch (the pointers below are never dereferenced)."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -27,6 +28,13 @@ def test_library_exports_every_declared_function():
     assert set(names) == set(sc.EXPORTED), names
     for name in names:
         assert hasattr(lib, name), name
+
+
+def test_the_entry_points_draw_on_nothing_that_throws():
+    """C callers cannot catch: the per-call tag comes from the clock, not from
+    std::random_device, whose constructor and calls may throw."""
+    out = subprocess.run(["nm", "-D", "--undefined-only", sc.LIB_PATH], capture_output=True, text=True, check=True)
+    assert "random_device" not in out.stdout
 
 
 def test_scale_rule_matches_oracle():
