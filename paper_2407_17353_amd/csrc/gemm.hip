@@ -1,19 +1,21 @@
 // Dispatch of the scaled FP8 GEMM over the four storage orders of A and B.
 #include "gemm4_kernel.h"
 
+#include <atomic>
+
 namespace scalify {
 
 int gemm4_grid(int tiles) {
   constexpr int kMaxDevices = 64;
-  static int cus[kMaxDevices];  // CUs per device, looked up once (a benign race)
+  static std::atomic<int> cus[kMaxDevices];  // CUs per device, looked up once
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) dev = -1;
-  int n = dev >= 0 ? cus[dev] : 0;
+  int n = dev >= 0 ? cus[dev].load(std::memory_order_relaxed) : 0;
   if (n <= 0) {
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) !=
             hipSuccess || n <= 0)
       n = 256;
-    if (dev >= 0) cus[dev] = n;
+    if (dev >= 0) cus[dev].store(n, std::memory_order_relaxed);
   }
   return tiles < n ? tiles : n;
 }

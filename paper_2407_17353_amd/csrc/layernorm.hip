@@ -16,6 +16,7 @@
 // 2048-column tiles that casts dx with the rescale the global amax gives and
 // accumulates the tile's partial parameter gradients, which a last kernel
 // sums over the row tiles in a fixed order.
+#include "kernels.h"
 #include "layernorm_dev.h"
 
 #include <stdlib.h>
@@ -229,20 +230,12 @@ int64_t layernorm_ws_floats(int64_t R, int64_t D) {
   return 4 * R + layernorm_row_tiles(R) * 2 * layernorm_param_stride(D);
 }
 
-// Workgroups of the row kernels: per_cu per CU (as many as their registers
-// let run at once), each walking rows with the grid's stride.
+// Workgroups of the row kernels: at most per_cu per CU, each walking rows with
+// the grid's stride.
 int ln_rows_grid(int64_t R, int wpr, int per_cu) {
-  static int cus = 0;  // (a benign race: every thread computes the same value)
-  if (cus <= 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-      n = 256;
-    cus = n;
-  }
   const int rpw = 4 / wpr;
   const int64_t need = (R + rpw - 1) / rpw;
-  const int64_t g = (int64_t)per_cu * cus;
+  const int64_t g = (int64_t)per_cu * gemm4_grid(1 << 30);  // (CUs of the current device)
   return (int)(need < 1 ? 1 : (need < g ? need : g));
 }
 

@@ -37,6 +37,19 @@ def test_the_entry_points_draw_on_nothing_that_throws():
     assert "random_device" not in out.stdout
 
 
+def test_writable_state_of_the_library():
+    """Every object that the library's host code may write between calls is one
+    of these, all safe with several threads and devices: the CU counts
+    (atomics, by device), the next tag (an atomic), and the scratch addresses
+    under their mutex."""
+    out = subprocess.run(["nm", "-C", sc.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    objects = re.findall(r"^\S+ [bBdD] (.*)$", out, flags=re.M)
+    mine = [o for o in objects if re.search(r"scalify::|\(anonymous namespace\)", o)
+            and not o.endswith(")") and not o.startswith("guard variable")]  # (not the kernels' handles)
+    # (scratch: the host's stand-in for the device array of that name, never read)
+    assert sorted(o.split("::")[-1] for o in mine) == ["cus", "g_scratch_mutex", "g_scratch_ptr", "next", "scratch"], mine
+
+
 def test_scale_rule_matches_oracle():
     for K in list(range(0, 3000)) + [8192, 11008, 12288, 16384, 1 << 40]:
         expect = orc.matmul_scale_log2(K) if K > 0 else 0
