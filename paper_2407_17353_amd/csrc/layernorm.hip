@@ -211,9 +211,13 @@ __global__ __launch_bounds__(64 * LN_PARAM_WAVES) void ln_params_kernel(const fl
   }
 }
 
-// Without rows there is no statistic: the apply kernel finds it 0.
-__global__ void ln_bwd_empty_kernel(uint32_t* hdr, const float* s_dy, const float* s_x) {
-  if (threadIdx.x == 0) stat_clear(hdr, s_dy, s_x);
+// Without rows: the output scale and a statistic of 0. (The workspace, which
+// may then have no bytes at all, is not touched.)
+__global__ void ln_bwd_empty_kernel(const float* s_dy, const float* s_x, float* out_scale, float* amax_out) {
+  if (threadIdx.x == 0) {
+    *out_scale = pow2_float(clamp_e8m0(pow2_exponent(s_dy) - pow2_exponent(s_x)));
+    if (amax_out) *amax_out = 0.0f;
+  }
 }
 
 static int row_grid(int64_t R) {
@@ -265,26 +269,24 @@ hipError_t launch_layernorm_fwd(const LnParams& p, int out_dtype, hipStream_t s)
 
 template <int XF>
 static void launch_bwd_xf(const LnParams& p, int out_dtype, hipStream_t s) {
-  if (p.R > 0) {
-    if (single_read_enabled())
-      launch_ln_bwd_rows<XF>(p, s);
-    else
-      hipLaunchKernelGGL((ln_bwd_stats_kernel<XF>), dim3(row_grid(p.R)), dim3(LN_THREADS), 0, s, p);
-  } else {
-    hipLaunchKernelGGL(ln_bwd_empty_kernel, dim3(1), dim3(64), 0, s, p.hdr, p.s_dy, p.s_x);
-  }
+  if (single_read_enabled())
+    launch_ln_bwd_rows<XF>(p, s);
+  else
+    hipLaunchKernelGGL((ln_bwd_stats_kernel<XF>), dim3(row_grid(p.R)), dim3(LN_THREADS), 0, s, p);
   launch_ln_apply<XF>(p, out_dtype, s);
 }
 
 hipError_t launch_layernorm_bwd(const LnParams& p, int out_dtype, hipStream_t s) {
-  if (p.x_fmt == kF16) launch_bwd_xf<kF16>(p, out_dtype, s);
+  if (p.R == 0)
+    hipLaunchKernelGGL(ln_bwd_empty_kernel, dim3(1), dim3(64), 0, s, p.s_dy, p.s_x, p.out_scale, p.amax_out);
+  else if (p.x_fmt == kF16) launch_bwd_xf<kF16>(p, out_dtype, s);
   else if (p.x_fmt == kF32) launch_bwd_xf<kF32>(p, out_dtype, s);
   else if (p.x_fmt == kE4M3) launch_bwd_xf<kE4M3>(p, out_dtype, s);
   else launch_bwd_xf<kE5M2>(p, out_dtype, s);
   if ((p.dgamma || p.dbeta) && p.D > 0)
     hipLaunchKernelGGL(ln_params_kernel, dim3((p.D + 63) / 64), dim3(64 * LN_PARAM_WAVES), 0, s,
                        p.partial + 4 * p.R,
-                       (int)layernorm_row_tiles(p.R), p.D, p.dgamma, p.dbeta);
+                       p.R ? (int)layernorm_row_tiles(p.R) : 0, p.D, p.dgamma, p.dbeta);
   return hipGetLastError();
 }
 

@@ -132,3 +132,25 @@ def test_layernorm_backward_replays():
         torch.cuda.synchronize()
         for got, ref in zip((dx.data, dx.scale, dg, db), want[i % 2]):
             assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("D", [1, 100, 8192, 8193, 20000])
+@pytest.mark.parametrize("mode", [sc.RESCALE_AMAX, sc.RESCALE_NONE])
+def test_layernorm_backward_without_rows(D, mode):
+    """R = 0: the scale of the rule, a statistic and parameter gradients of 0;
+    nothing is written outside the workspace, which at D > 8192 has no bytes."""
+    say(f"case layernorm backward R=0 D={D} mode={mode}")
+    need = sc.scalify_layernorm_bwd_workspace_size(0, D)
+    assert (need == 0) == (D > 8192)
+    buf = torch.full((need + (1 << 20),), 0xAB, dtype=torch.uint8, device=DEV)
+    assert buf.data_ptr() % 256 == 0
+    empty = lambda fmt, e: sc.ScaledArray(torch.empty((0, D), dtype=sc.STORAGE_DTYPE[fmt], device=DEV), fmt,
+                                          sc.scale_tensor(e, DEV))
+    dx = empty(sc.E5M2, 0)
+    dg, db, am = (torch.full((n,), 7.0, device=DEV) for n in (D, D, 1))
+    sc.scalify_layernorm_bwd(empty(sc.E5M2, 5), empty(sc.F16, 2), dx, rescale=mode, dgamma=dg, dbeta=db,
+                             amax_out=am, ws=buf)
+    torch.cuda.synchronize()
+    assert dx.scale.item() == 2.0 ** 3 and am.item() == 0.0
+    assert not dg.any() and not db.any()
+    assert bool((buf[need:] == 0xAB).all())
