@@ -11,7 +11,11 @@ these kernels and fails if, in any kernel that uses those accumulators, any
 instruction other than the accumulator asm's own forms (an MFMA whose
 destination and C operand are the same a[n:n+3], a write of 0, a read into a
 VGPR) names one of them -- the compiler spilling into it or using it as the
-data of a load or an MFMA operand -- or the kernel uses scratch memory.
+data of a load or an MFMA operand.
+
+No GEMM kernel may use scratch memory, but for the fused epilogue of the 8-wave
+kernel (gemm_*_fused), which holds accumulators, residual codes and channel
+exponents at once and keeps some of them there.
 
 The loads of these kernels are inline asm too, so the compiler does not keep
 the distance their scalar operands need: the build fails if a vector memory
@@ -110,12 +114,23 @@ def _agprs(insn: str) -> set:
     return regs
 
 
+_MID_KERNEL = re.compile(r"mid_gemm_kernelILb[01]ELb[01]ELi\d+ELi\d+ELi(\d+)ELi\d+EEE")
+
+
 def pinned_kernel(src: str, name: str) -> bool:
-    """Whether a kernel of this source keeps its accumulators in asm-named
-    AGPRs: every MFMA kernel of the gemm_* sources, and of the mid_* sources
-    those with 256 columns (8 accumulator tiles per row of tiles)."""
+    """Whether a kernel of this source that multiplies into AGPRs keeps its
+    accumulators in asm-named ones: every such kernel of the gemm_* sources,
+    and of the mid_* sources those with 256 columns (8 accumulator tiles per
+    row of tiles); the others leave their accumulators to the compiler."""
     base = os.path.basename(src)
-    return base.startswith("gemm_") or (base.startswith("mid_") and "ELi8ELi3EEEv" in name)
+    if base.startswith("gemm_"):
+        return True
+    if base.startswith("mid_"):
+        m = _MID_KERNEL.search(name)
+        if not m:
+            raise RuntimeError(f"{base}: which accumulators does {name} hold? (its name has another form)")
+        return m.group(1) == "8"
+    return False
 
 
 def check_code(obj: str, tmp: str) -> int:
@@ -140,17 +155,26 @@ def check_code(obj: str, tmp: str) -> int:
             kernels[name] = []
         elif name is not None:
             kernels[name].append(line)
+    return check_functions(obj, kernels)
+
+
+def check_functions(obj: str, kernels: dict) -> int:
+    """The checks of check_code on disassembled functions: name -> lines."""
+    base = os.path.basename(obj).split(".")[0]
     checked = 0
     for name, body in kernels.items():
         insns = [line.split("//")[0].strip() for line in body]
         near = scalar_distance_violations(insns)
         if near:
             raise RuntimeError(f"{obj}: {name} reads a scalar register too soon: {near[:4]}")
+        spills = [l for l in insns if l.startswith("scratch_")]
+        if spills and not base.endswith("_fused"):
+            raise RuntimeError(f"{obj}: {name} uses scratch memory: {spills[:4]}")
         if not any(_AGPR_MFMA.search(l) for l in insns):
             # Out-of-line functions that the kernels call while accumulators
             # still sit in AGPRs must leave AGPRs alone.
             bad = [l for l in insns if _ANY_AGPR.search(l)]
-            if bad and os.path.basename(obj).startswith("gemm_"):
+            if bad and base.startswith("gemm_"):
                 raise RuntimeError(f"{obj}: function {name} uses AGPRs: {bad[:4]}")
             continue
         if not pinned_kernel(obj, name):
@@ -160,11 +184,13 @@ def check_code(obj: str, tmp: str) -> int:
         for insn in insns:
             if _AGPR_MFMA.search(insn):
                 held |= _agprs(insn)
-        bad = [insn for insn in insns
-               if "scratch_" in insn or (_agprs(insn) & held and not _asm_agpr_form(insn))]
+        bad = [insn for insn in insns if _agprs(insn) & held and not _asm_agpr_form(insn)]
         if bad:
-            raise RuntimeError(f"{obj}: kernel {name} has compiler-placed AGPR or scratch "
-                               f"accesses next to the asm-held accumulators: {bad[:4]}")
+            raise RuntimeError(f"{obj}: kernel {name} has compiler-placed AGPR accesses next to the "
+                               f"asm-held accumulators: {bad[:4]}")
+    # (of the mid_* sources, one kernel with 256 columns for each pair of formats)
+    if re.fullmatch("mid_[nt][nt]", base) and checked != 4:
+        raise RuntimeError(f"{obj}: {checked} kernels with asm-held accumulators, not 4")
     return checked
 
 
