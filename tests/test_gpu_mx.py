@@ -21,6 +21,7 @@ import torch
 from oracle import oracle as orc
 from paper_2407_17353_amd import binding as sc
 from paper_2407_17353_amd import workloads as wl
+from tests.gemm_kinds import MX, MX_INSIDE
 from tests.helpers import FMT, _compare_acc, check_p1, record, say, stored_with_padding
 
 pytestmark = pytest.mark.gpu
@@ -280,8 +281,19 @@ def test_interior_path_equals_the_checked_path(mode, fout):
     tiles cast or stored without per-element checks, the single pass where
     it runs) give the codes, scale and statistic of the same call with the
     export, which P1 checks."""
-    M, N, K = 512, 384, 512
-    say(f"case mx interior {mode} fout={fout}")
+    _interior((512, 384, 512), mode, fout)
+
+
+@pytest.mark.parametrize("mode", list(MODES))
+@pytest.mark.parametrize("fout", [sc.E4M3, sc.E5M2, sc.F16])
+@pytest.mark.parametrize("kernel", list(MX_INSIDE))
+def test_interior_path_of_the_large_kernels(mode, fout, kernel):
+    _interior(MX_INSIDE[kernel], mode, fout)
+
+
+def _interior(shape, mode, fout):
+    M, N, K = shape
+    say(f"case mx interior {shape} {mode} fout={fout}")
     A = _codes((M, K), 0, 960)
     B = _codes((K, N), 1, 961)
     PA = wl.mx_block_scales(M, K, 962)
@@ -292,3 +304,43 @@ def test_interior_path_equals_the_checked_path(mode, fout):
     assert np.array_equal(fast[0], run[0]), f"{np.count_nonzero(fast[0] != run[0])} codes differ"
     assert fast[1] == run[1] and np.float32(fast[2]) == np.float32(run[2])
     _check(run, A, 0, False, -1, B, 1, False, 2, fout, PA, PB, MODES[mode], amax_in=3.0)
+
+
+@pytest.mark.parametrize("mode", list(MODES))
+@pytest.mark.parametrize("ta,tb", LAYOUTS, ids=lambda v: "T" if v else "N")
+@pytest.mark.parametrize("kernel", list(MX))
+def test_block_scales_of_the_large_kernels(kernel, ta, tb, mode, monkeypatch):
+    """Every kernel that large block-scaled outputs take, ragged in M, N and K:
+    P1 on every code, P2 on a sample; without the export, and in the dynamic
+    rescale's other ways (GEMM + cast kernel, the recovery of a grid that gave
+    up), the same bits."""
+    M, N, K = MX[kernel]
+    i = 2 * ta + tb + list(MODES).index(mode) + list(MX).index(kernel)
+    fa, fb, fout = [(0, 0), (1, 0), (0, 1), (1, 1)][i % 4] + ([sc.E4M3, sc.F16, sc.E5M2][i % 3],)
+    say(f"case mx {kernel} {M}x{N}x{K} {mode} ta={ta} tb={tb} fmts={fa},{fb}->{fout}")
+    A, B = _codes((M, K), fa, 970 + i), _codes((K, N), fb, 971 + i)
+    A_st = A.t().contiguous() if ta else A
+    B_st = B.t().contiguous() if tb else B
+    PA, PB = wl.mx_block_scales(M, K, 972 + i), wl.mx_block_scales(N, K, 973 + i)
+    args = (A_st, fa, ta, -1, B_st, fb, tb, 2, fout, PA, PB, MODES[mode])
+    codes, e_out, amax, acc = run = _mx_run(*args, amax_in=3.0)
+    if mode == "delayed":
+        rc, re, ra = orc.matmul_epilogue_delayed(acc, 0.5, 4.0, K, 3.0, 0, True, fout)
+        assert e_out == re and np.float32(amax) == np.float32(ra) and np.array_equal(codes, rc)
+    else:
+        check_p1(codes, e_out, amax, acc, K, -1, 2, fout, MODES[mode])
+    rng = np.random.default_rng(974)
+    ii = np.concatenate([rng.integers(0, M, 2048), [0, 0, M - 1, M - 1]])
+    jj = np.concatenate([rng.integers(0, N, 2048), [0, N - 1, 0, N - 1]])
+    ref, l1 = orc.matmul_acc_mx_at(A_st.numpy(), fa, ta, B_st.numpy(), fb, tb, PA.numpy(), PB.numpy(), ii, jj)
+    _compare_acc(acc[ii, jj], ref, l1, K)
+    others = [_mx_run(*args, amax_in=3.0, want_acc=False)]
+    if mode == "amax":
+        monkeypatch.setenv("SCALIFY_SINGLE_PASS", "0")
+        others.append(_mx_run(*args))
+        monkeypatch.setenv("SCALIFY_SINGLE_PASS", "1")
+        monkeypatch.setenv("SCALIFY_SPIN_TICKS", "0")
+        others.append(_mx_run(*args))
+    for other in others:
+        assert np.array_equal(other[0], run[0]) and other[1:3] == run[1:3]
+        assert other[3] is None or np.array_equal(other[3].view(np.uint32), run[3].view(np.uint32))

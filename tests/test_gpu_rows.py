@@ -41,9 +41,24 @@ WIDTHS = [1, 15, 64, 1023, 1024, 1040, 2047, 2048, 2049, 3072, 4095, 4096, 4097,
 @pytest.mark.parametrize("fx,fd,fo", [(sc.F16, sc.E5M2, sc.E5M2), (sc.F32, sc.F16, sc.F16), (sc.E4M3, sc.F32, sc.E4M3)],
                          ids=["f16-e5m2", "f32-f16", "e4m3-f32"])
 def test_single_read_equals_multi_pass(D, fx, fd, fo, monkeypatch):
-    R = 7 if D > 64 else 4100
-    say(f"case layernorm rows R={R} D={D} fmts={fx},{fd}->{fo}")
+    _single_equals_multi(7 if D > 64 else 4100, D, fx, fd, fo, monkeypatch)
+
+
+# more rows than the grid has places (768 or 1024 workgroups of 1, 2 or 4 rows
+# on 256 CUs): the next row's loads, the reuse of the sums' LDS slots and the
+# statistic's early fold (more than two rounds of rows), by waves per row
+@pytest.mark.parametrize("R,D", [(6300, 72), (6200, 2048), (3200, 2049), (3100, 4096), (1700, 4100), (1600, 8192)])
+@pytest.mark.parametrize("fx,fd,fo", [(sc.F16, sc.E5M2, sc.E5M2), (sc.F32, sc.F16, sc.F16)], ids=["f16-e5m2", "f32-f16"])
+def test_single_read_equals_multi_pass_over_many_rows(R, D, fx, fd, fo, monkeypatch):
+    for peak in (0, R - 2):  # the largest gradient among the first rows and the last
+        _single_equals_multi(R, D, fx, fd, fo, monkeypatch, peak)
+
+
+def _single_equals_multi(R, D, fx, fd, fo, monkeypatch, peak=None):
+    say(f"case layernorm rows R={R} D={D} fmts={fx},{fd}->{fo} peak={peak}")
     x, dy = _rows(R, D, fx, D), _rows(R, D, fd, D + 1, 10.0)
+    if peak is not None:
+        dy.data[peak, D // 3] = torch.tensor([1000.0], device=DEV).to(TORCH[fd]).view(dy.data.dtype)[0]
     gamma = 1.0 + 0.1 * torch.randn(D, device=DEV)
     beta = 0.1 * torch.randn(D, device=DEV)
     res = []
@@ -58,6 +73,7 @@ def test_single_read_equals_multi_pass(D, fx, fd, fo, monkeypatch):
         sc.scalify_layernorm_bwd(dy, x, dx, gamma=gamma, dgamma=dg, dbeta=db, amax_out=am, pre_out=pre_b, ws=ws)
         torch.cuda.synchronize()
         assert am.item() == pre_b.abs().max().item()
+        assert peak is None or am.item() == pre_b[peak].abs().max().item()
         res.append([t.contiguous().view(torch.uint8).cpu().numpy()
                     for t in (y.data, pre, dx.data, dx.scale, pre_b, dg, db, am)])
     for a, b in zip(*res):

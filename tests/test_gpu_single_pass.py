@@ -1,11 +1,11 @@
 """GPU tests of the single-pass dynamic rescale and of the direct cast of the
-persistent GEMM kernel (through the C ABI).
+GEMM kernels (through the C ABI).
 
-The single pass keeps each workgroup's last tile in its accumulators, meets
-the other workgroups at a grid barrier on the amax statistic (Section 3.3),
-casts that tile directly and its earlier tiles from the intermediate. AMAX
-calls without a fused epilogue take it by default where every workgroup of
-the persistent grid holds one tile; SCALIFY_SINGLE_PASS=1 forces it
+The single pass keeps each workgroup's last tile (in its accumulators, LDS or
+registers, by kernel), meets the other workgroups at a grid barrier on the amax
+statistic (Section 3.3), casts that tile directly and, in the 256 x 256 kernel,
+its earlier tiles from the intermediate. AMAX calls take it by default where
+the grid's workgroups hold their tiles; SCALIFY_SINGLE_PASS=1 forces it
 wherever it can run, =0 never. It must give exactly the codes, scale and
 statistic of the two-kernel path (GEMM + cast kernel), which the matmul
 tests check against the oracle, and P1 against the oracle on the GPU's
@@ -32,6 +32,7 @@ import torch
 from oracle import oracle as orc
 from paper_2407_17353_amd import binding as sc
 from paper_2407_17353_amd import workloads as wl
+from tests.gemm_kinds import PLAIN, PLAIN_INSIDE
 from tests.helpers import check_p1, gpu_matmul, say, stored_with_padding
 
 pytestmark = pytest.mark.gpu
@@ -69,7 +70,7 @@ def run(A_st, fa, ta, sa, B_st, fb, tb, sb, fout, mode=sc.RESCALE_AMAX, want_acc
     acc = torch.empty((M, N), dtype=torch.float32, device=DEV) if want_acc else None
     amax = torch.empty(1, dtype=torch.float32, device=DEV)
     ws = sc.workspace(sc.scalify_matmul_workspace_size(M, N, fout, mode), DEV)
-    ws[:256].fill_(0xAB)  # the prologue must clear what the kernel relies on
+    ws[:256].fill_(0xAB)  # the call must clear what it relies on
     sc.scalify_matmul(a, b, out, rescale=mode, acc_out=acc, amax_out=amax, ws=ws)
     torch.cuda.synchronize()
     codes = out.data.cpu().numpy()
@@ -83,8 +84,8 @@ def run(A_st, fa, ta, sa, B_st, fb, tb, sb, fout, mode=sc.RESCALE_AMAX, want_acc
             acc.cpu().numpy() if want_acc else None, state)
 
 
-# tiles of 256 x 256: 1 (one workgroup), 24 (one per workgroup, edges),
-# 272 (more tiles than CUs: 16 workgroups hold a second tile), 512 (2 rounds)
+# wave kernel, 128 x 128 pairs, and 256 x 256 tiles: 272 (more tiles than CUs:
+# 16 workgroups hold a second tile), 512 (2 rounds)
 SHAPES = [(200, 130, 300), (1024, 1500, 640), (4352, 4096, 256), (4096, 8192, 384)]
 
 
@@ -137,9 +138,17 @@ def test_single_pass_abort_recovery(shape, fout):
 
 def test_single_pass_specials():
     """NaN / Inf accumulators through the single pass: NaN codes keep their
-    sign, the Inf row dominates the statistic (no rescale)."""
-    say("case single-pass specials")
-    M, N, K = 300, 520, 256
+    sign, the Inf row dominates the statistic (no rescale). (wave kernel)"""
+    _single_pass_specials(300, 520, 256)
+
+
+@pytest.mark.parametrize("kernel", list(PLAIN))
+def test_single_pass_specials_of_the_large_kernels(kernel):
+    _single_pass_specials(*PLAIN[kernel])
+
+
+def _single_pass_specials(M, N, K):
+    say(f"case single-pass specials {M}x{N}x{K}")
     A = _codes((M, K), sc.E5M2, 81).numpy().copy()
     B = _codes((K, N), sc.E5M2, 82).numpy().copy()
     A[3, 7] = 0x7F   # NaN
@@ -158,9 +167,21 @@ def test_single_pass_specials():
 def test_extreme_scales_outside_the_conversion_window(mode, sa, sb, fout):
     """Input scales at the E8M0 ends: the output scale clamps at 2^+-127, so
     the cast's shift leaves [-126, 126] (scaled by v_ldexp first) in NONE
-    mode; P1 against the oracle on the GPU accumulator."""
-    M, N, K = 300, 260, 200
-    say(f"case extreme scales mode={mode} sa={sa} sb={sb} fout={fout}")
+    mode; P1 against the oracle on the GPU accumulator. (wave kernel)"""
+    _extreme_scales((300, 260, 200), mode, sa, sb, fout)
+
+
+@pytest.mark.parametrize("mode", [sc.RESCALE_NONE, sc.RESCALE_AMAX])
+@pytest.mark.parametrize("sa,sb", [(-127, -127), (127, 127)])
+@pytest.mark.parametrize("kernel", list(PLAIN))
+def test_extreme_scales_of_the_large_kernels(mode, sa, sb, kernel):
+    fout = [sc.E4M3, sc.E5M2, sc.F16][(list(PLAIN).index(kernel) + mode + (sa > 0)) % 3]
+    _extreme_scales(PLAIN[kernel], mode, sa, sb, fout)
+
+
+def _extreme_scales(shape, mode, sa, sb, fout):
+    M, N, K = shape
+    say(f"case extreme scales {shape} mode={mode} sa={sa} sb={sb} fout={fout}")
     A = _codes((M, K), sc.E4M3, 91)
     B = _codes((K, N), sc.E4M3, 92)
     codes, e_out, amax, acc = gpu_matmul(A, sc.E4M3, False, sa, B, sc.E4M3, False, sb, fout, mode)
@@ -222,9 +243,27 @@ def test_direct_cast_interior_path_equals_the_checked_path(mode, fout, sat):
     scale and statistic of the per-element path that the same call takes
     when it exports its accumulators, which P1 checks against the oracle.
     Heavy-range E5M2 inputs overflow the output formats; NaN and Inf
-    accumulators sit in interior wave tiles."""
-    say(f"case direct interior mode={mode} fout={fout} sat={sat}")
-    M, N, K = 512, 384, 256
+    accumulators sit in interior tiles. (wave kernel)"""
+    _direct_interior(PLAIN_INSIDE["wave"], mode, fout, sat)
+
+
+@pytest.mark.parametrize("mode", [sc.RESCALE_NONE, sc.RESCALE_DELAYED])
+@pytest.mark.parametrize("fout", [sc.E4M3, sc.E5M2, sc.F16])
+@pytest.mark.parametrize("sat", [True, False], ids=["sat", "nosat"])
+def test_direct_cast_interior_path_of_256_x_256_tiles(mode, fout, sat):
+    _direct_interior(PLAIN_INSIDE["big"], mode, fout, sat)
+
+
+@pytest.mark.parametrize("mode", [sc.RESCALE_NONE, sc.RESCALE_DELAYED])
+@pytest.mark.parametrize("kernel", list(PLAIN))
+def test_direct_cast_of_the_large_kernels_at_ragged_edges(mode, kernel):
+    for i, sat in enumerate((True, False)):
+        _direct_interior(PLAIN[kernel], mode, [sc.E4M3, sc.E5M2, sc.F16][(list(PLAIN).index(kernel) + i) % 3], sat)
+
+
+def _direct_interior(shape, mode, fout, sat):
+    M, N, K = shape
+    say(f"case direct interior {shape} mode={mode} fout={fout} sat={sat}")
     A = _codes((M, K), sc.E5M2, 131, heavy=True).numpy().copy()
     B = _codes((K, N), sc.E5M2, 132, heavy=True).numpy().copy()
     A[3, 7] = 0x7F     # NaN row
@@ -252,9 +291,20 @@ def test_dynamic_rescale_interior_path_equals_the_checked_path(single_pass, fout
     """The dynamic rescale without an exported accumulator (interior wave
     tiles stored without per-element checks, or held by the single pass)
     gives the codes, scale and statistic of the same call with the export,
-    which P1 checks against the oracle."""
-    say(f"case dynamic interior single_pass={single_pass} fout={fout} sat={sat}")
-    M, N, K = 512, 384, 256
+    which P1 checks against the oracle. (wave kernel)"""
+    _dynamic_interior(PLAIN_INSIDE["wave"], single_pass, fout, sat)
+
+
+@pytest.mark.parametrize("single_pass", [0, 1], ids=["pair", "single"])
+@pytest.mark.parametrize("fout", [sc.E4M3, sc.E5M2, sc.F16])
+@pytest.mark.parametrize("sat", [True, False], ids=["sat", "nosat"])
+def test_dynamic_rescale_interior_path_of_256_x_256_tiles(single_pass, fout, sat):
+    _dynamic_interior(PLAIN_INSIDE["big"], single_pass, fout, sat)
+
+
+def _dynamic_interior(shape, single_pass, fout, sat):
+    M, N, K = shape
+    say(f"case dynamic interior {shape} single_pass={single_pass} fout={fout} sat={sat}")
     A = _codes((M, K), sc.E5M2, 141, heavy=True).numpy().copy()
     B = _codes((K, N), sc.E5M2, 142, heavy=True).numpy().copy()
     A[3, 7] = 0x7F
