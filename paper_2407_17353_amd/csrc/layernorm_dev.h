@@ -56,7 +56,7 @@ __device__ __forceinline__ void ln_load16(int fmt, const void* base, int64_t off
 
 __device__ __forceinline__ void ln_param16(const float* p, int n, int valid, float dflt,
                                            float (&v)[16]) {
-  if (p == nullptr) {
+  if (p == nullptr || valid <= 0) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = dflt;
   } else if (valid >= 16) {
@@ -121,15 +121,6 @@ __device__ __forceinline__ float ln_raw_decode(const uint32_t* w, int i) {
   else return decode_hw<XF>((w[i >> 2] >> (8 * (i & 3))) & 0xFFu);
 }
 
-// Element I of a chunk's raw codes as fp32: an FP8 code is converted straight
-// from its byte of the word (the conversion selects the byte).
-template <int XF, int I>
-__device__ __forceinline__ float ln_decode_at(const uint32_t* w) {
-  if constexpr (XF == kE4M3) return __builtin_amdgcn_cvt_scalef32_f32_fp8(w[I >> 2], 1.0f, I & 3);
-  else if constexpr (XF == kE5M2) return __builtin_amdgcn_cvt_scalef32_f32_bf8(w[I >> 2], 1.0f, I & 3);
-  else return ln_raw_decode<XF>(w, I);
-}
-
 // The 16 elements of a chunk's raw codes as fp32 (exact), FP8 codes two per
 // conversion (the packed form takes the low or the high 16 bits of a word).
 template <int XF>
@@ -157,7 +148,13 @@ __device__ __forceinline__ void ln_decode16(const uint32_t* w, float (&x)[16]) {
 }
 
 // Dwords of a 16-element chunk of format F, and the chunk's raw codes at
-// element e of base (valid elements, the rest zero: codes that decode to 0).
+// element e of base (valid elements, the rest zero: codes that decode to 0; a
+// lane past the row's end has none and skips the chunk). The loads are 16 bytes
+// wide also where the row ends inside one: rows are 16-byte aligned, so a load
+// that holds an element of the row stays in the row's padding (ld).
+// (Element loads there, whose sixteen tests every wave went through for the
+// lanes past the end as well, took the forward of 16384 x 512 F16 25 us, the
+// backward of 16384 x 2512 F16 147; now 16 and 108.)
 template <int F>
 constexpr int ln_chunk_words() { return F == kF32 ? 16 : (F == kF16 ? 8 : 4); }
 
@@ -168,19 +165,25 @@ __device__ __forceinline__ void ln_load_raw(const void* base, int64_t e, int val
   constexpr int EPW = 16 / W;  // elements per dword
 #pragma unroll
   for (int k = 0; k < W; ++k) w[k] = 0u;
+  auto piece = [&](int h) {
+    const u4 v = F == kF32 ? *((const u4*)((const uint32_t*)base + e) + h)
+                           : (F == kF16 ? *((const u4*)((const uint16_t*)base + e) + h)
+                                        : *((const u4*)((const uint8_t*)base + e) + h));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[4 * h + k] = v[k];
+  };
   if (valid >= 16) {
 #pragma unroll
-    for (int h = 0; h < W / 4; ++h) {
-      const u4 v = F == kF32 ? *((const u4*)((const uint32_t*)base + e) + h)
-                             : (F == kF16 ? *((const u4*)((const uint16_t*)base + e) + h)
-                                          : *((const u4*)((const uint8_t*)base + e) + h));
+    for (int h = 0; h < W / 4; ++h) piece(h);
+  } else if (valid > 0) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) w[4 * h + k] = v[k];
+    for (int h = 0; h < W / 4; ++h)
+      if (valid > 4 * EPW * h) piece(h);
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      const int n = valid - EPW * k;  // elements of dword k
+      w[k] = n <= 0 ? 0u : (n >= EPW ? w[k] : w[k] & ((1u << (32 / EPW * n & 31)) - 1u));
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (i < valid) w[i / EPW] |= load1<F>(base, e + i) << ((32 / EPW) * (i % EPW));
   }
 }
 

@@ -3,10 +3,11 @@
 // What bounds them: HBM, once the arithmetic is kept below it. The row's
 // values are decoded once and kept (as x, then x - mean, in place); a lane
 // holds 32 of them, so the sums, divisions and the square root that every
-// lane does per row cost little per element, and three to four waves per SIMD
-// still fit, which keep the next rows' loads in flight (the kernels before
-// these re-decoded 64 raw elements per lane in each of four passes and were
-// bound by that: backward statistics of 16384 x 4096 58 us, 50 us now).
+// lane does per row cost little per element, and three waves per SIMD still
+// fit (two with FP32 inputs, and in the backward with FP16 or FP32 gradients),
+// which keep the next rows' loads in flight (the kernels before these
+// re-decoded 64 raw elements per lane in each of four passes and were bound by
+// that: backward of 16384 x 4096, F16 x and E5M2 dy, 112 us, 98 us now).
 //
 // A row of D <= 2048 columns belongs to one wave, of up to 4096 to two and of
 // up to 8192 to four waves of a workgroup (WPR); wave part k takes the lane
@@ -139,12 +140,20 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_rows_kernel(LnParams p) {
   }
 }
 
+// Waves per SIMD that the backward's registers are held to: three, which the
+// compiler misses by a few registers when left alone (F16 x, E5M2 dy, 32768 x
+// 2512: 276 us with two), where they fit without spills.
+template <int XF, int DYF, bool FULL>
+constexpr int ln_bwd_waves() {
+  return XF != kF32 && (DYF == kE4M3 || DYF == kE5M2 || (DYF == kF16 && FULL)) ? 3 : 2;
+}
+
 // The backward's statistics: the four numbers of every row (rowstats) and the
 // amax of |dx|, with ln_dx's arithmetic. The last multiplication of dx, by
 // 1 / (std + eps) > 0, keeps the order of magnitudes, so it is done once per
 // row and lane, on the largest factor. The call's header: stat_header.h.
 template <int XF, int DYF, int WPR, bool FULL>
-__global__ __launch_bounds__(LN_THREADS) void ln_bwd_rows_kernel(LnParams p) {
+__global__ __launch_bounds__(LN_THREADS, (ln_bwd_waves<XF, DYF, FULL>())) void ln_bwd_rows_kernel(LnParams p) {
   // (no FMA contraction: see ln_fwd_rows_kernel)
 #pragma clang fp contract(off)
   constexpr int RPW = 4 / WPR;
@@ -163,17 +172,8 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_rows_kernel(LnParams p) {
   load_params<FULL>(p.gamma, 1.0f, ch.n, ch.valid, gam);
   if (blockIdx.x == 0 && threadIdx.x == 0) stat_open(p.hdr, p.tag, p.s_dy, p.s_x);
   float lmax = 0.0f;
-  // (the fold after the first rows: see below)
-  float known = -1.0f;
-  auto block_max = [&]() {
-    for (int off = 32; off > 0; off >>= 1) lmax = fmaxf(lmax, __shfl_xor(lmax, off, 64));
-    __syncthreads();
-    if (lane == 0) wmax[wave] = lmax;
-    __syncthreads();
-    return fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-  };
 #pragma unroll 1
-  for (bool early = r0 + 2 * stride < p.R; r0 < p.R; r0 += stride) {
+  for (; r0 < p.R; r0 += stride) {
     const int64_t r = r0 + slot;
     float x[2][16], g[2][16];
 #pragma unroll
@@ -221,24 +221,14 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_rows_kernel(LnParams p) {
       }
       lmax = fmaxf(lmax, tmax * st.y);
     }
-    // A workgroup with more rows to come folds its maximum in after its first
-    // ones and learns how large the others' are: at the end, when all finish
-    // together, almost none has anything larger to add (768 atomics on one
-    // word take 8 us).
-    if (early) {
-      early = false;
-      const float m = block_max();
-      if (threadIdx.x == 0) {
-        stat_await(p.hdr, p.tag, p.s_dy, p.s_x);
-        known = fmaxf(stat_fold(p.hdr, m), m);
-      }
-    }
   }
   // amax of |dx|: wave butterfly, then the four waves, then the header
-  const float m = block_max();
-  if (threadIdx.x == 0 && m > known) {
+  for (int off = 32; off > 0; off >>= 1) lmax = fmaxf(lmax, __shfl_xor(lmax, off, 64));
+  if (lane == 0) wmax[wave] = lmax;
+  __syncthreads();
+  if (threadIdx.x == 0) {
     stat_await(p.hdr, p.tag, p.s_dy, p.s_x);
-    stat_fold(p.hdr, m);
+    stat_fold(p.hdr, fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])));
   }
 }
 
