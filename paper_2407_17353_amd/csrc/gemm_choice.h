@@ -43,17 +43,28 @@ struct GemmChoice {
 //   256 x 256 tiles. A deeper ring (one workgroup to a CU) or the larger tile
 //   for long K: 2048x2048x8192 56.6 / 51.9, 2048x4096x8192 72.3 / 63.7
 //   (256 x 256: 87.4).
+//   With a statistic, the two atomics of each workgroup on one line weigh where
+//   there are many and K is short: 256 x 256 tiles again. AMAX, against these,
+//   512 workgroups, 2048x4096xK: K 64 22.9 / 19.8, 512 25.2 / 22.3, 1024 27.2 /
+//   26.2, 1536 30.1 / 31.0; 384 workgroups, 1536x4096xK: K 64 19.5 / 18.7, 512
+//   21.5 / 21.1, 768 22.1 / 23.3.
 // - Else 256 x 256 tiles; with a fused epilogue, which that kernel has only in
 //   its slower 8-wave form, 128 x 128 tiles where these fill their rounds of
 //   512 that much better than 256 x 256 tiles fill rounds of 256 (a round of
 //   them takes 9/16 of the other's time): bias and GELU 3001x8192x2048 (3 and
-//   2 rounds) 90.5 against 102.0, 4096x8192x2048 (4 and 2) 118 / 112,
-//   8192x8192x2048 304 / 243. (Without one: 3001x8192x2048 71.7 / 65.4.)
-// The choice depends on the sizes and on what is fused, not on the rescale
-// mode, so the modes of a call (and the single pass, the kernel pair and the
-// recovery) sum K in one order. Calls of other sizes need not: the wave kernel
-// sums four interleaved shares of K, the others go through K in order.
-inline GemmChoice gemm_choice(int64_t M, int64_t N, int64_t K, int cus, bool fused, bool mx) {
+//   2 rounds) 93.7 against 100.7, 4096x8192x2048 (4 and 2) 118 / 112,
+//   8192x8192x2048 304 / 243. (Without one: 3001x8192x2048 71.7 / 65.4.) Not
+//   where operands and fp32 intermediate outgrow the 256 MiB last-level cache,
+//   from which the smaller tiles read their panels more often: AMAX
+//   3001x12288x5504 (231 MB) 247 / 255, 2048x12288x11008 (258 MB) 329 / 286,
+//   3001x12288x8192 (272 MB) 355 / 336; direct casts, without an intermediate,
+//   304 / 331 at the last one.
+// Calls of one size and kind sum K in one order in every mode: all kernels but
+// the wave kernel and the block-scaled ones go through K alike. Calls of other
+// sizes need not: the wave kernel sums four interleaved shares of K.
+// amax: dynamic rescale; statistic: it or another call that reports one.
+inline GemmChoice gemm_choice(int64_t M, int64_t N, int64_t K, int cus, bool fused, bool mx, bool amax,
+                              bool statistic) {
   auto make = [&](GemmKind k, int tm, int tn, MidTile t = MID_256) {
     return GemmChoice{k, tm, tn, ((M + tm - 1) / tm) * ((N + tn - 1) / tn), t, t == MID_128_PAIR ? 2 : 1};
   };
@@ -64,8 +75,12 @@ inline GemmChoice gemm_choice(int64_t M, int64_t N, int64_t K, int cus, bool fus
   const GemmChoice pair = make(GEMM_MID, kMidTM, 128, MID_128_PAIR);
   if (mx) return wave.tiles <= kWaveHeld * cus ? wave : big;
   if (wave.tiles <= cus) return wave;
+  if (mid8.tiles <= cus && !fused && statistic &&
+      ((K <= 512 && 2 * pair.tiles >= 3 * cus) || (K <= 1024 && 4 * pair.tiles > 7 * cus)))
+    return big;
   if (mid8.tiles <= cus) return K < 4096 ? pair : mid4.tiles <= cus ? mid4 : mid8;
   if (!fused) return big;
+  if (amax && M * K + K * N + 4 * M * N > 240000000) return big;
   const int64_t big_rounds = (big.tiles + cus - 1) / cus, pair_rounds = (pair.tiles + 2 * cus - 1) / (2 * cus);
   return 9 * pair_rounds < 16 * big_rounds ? pair : big;
 }

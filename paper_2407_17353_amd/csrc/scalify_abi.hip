@@ -351,7 +351,12 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
   const bool tn_mx = mx && a->trans != 0 && b->trans == 0;
   const bool persistent = persistent_enabled();
   const int cus = gemm4_grid(1 << 30);
-  const GemmChoice gc = gemm_choice(M, N, K, cus, fused, mx);
+  // The direct cast needs the header only for a statistic, or where the
+  // output scale shares memory with what other workgroups still read.
+  const float* o = out->scale;
+  const bool counted = !amax_mode && (opts->amax_out || o == a->scale || o == b->scale ||
+                                      (res && o == res->scale) || (delayed && o == opts->amax_in));
+  const GemmChoice gc = gemm_choice(M, N, K, cus, fused, mx, amax_mode, amax_mode || counted);
   int grid = (int)gc.tiles;
   if (persistent && gc.kind != GEMM_FUSED && grid > gc.resident * cus) grid = gc.resident * cus;
   // Single pass where each workgroup can hold its tiles: the wave kernel by
@@ -404,11 +409,7 @@ scalify_status scalify_matmul(const scalify_scaled_array* a, const scalify_scale
   p.s_res = res ? res->scale : nullptr;
   p.amax_in = delayed ? opts->amax_in : nullptr;
   p.residual = res ? 1 : 0;
-  // The direct cast needs the header only for a statistic, or where the
-  // output scale shares memory with what other workgroups still read.
-  const float* o = out->scale;
-  p.counted = epi == EPI_DIRECT &&
-              (opts->amax_out || o == p.s0 || o == p.s1 || o == p.s_res || o == p.amax_in);
+  p.counted = counted;
   p.uses_header = epi != EPI_DIRECT || p.counted;
   p.tag = p.uses_header ? next_tag() : 0;
   p.sat = opts->saturate != 0;

@@ -19,8 +19,9 @@ def kinds(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", os.path.join(HERE, "host_gemm_choice.cpp"),
                     "-o", exe], check=True)
 
-    def of(calls):
-        text = "".join(f"{M} {N} {K} {CUS} {int(fused)} {int(mx)}\n" for M, N, K, fused, mx in calls)
+    def of(calls, mode="amax"):
+        flags = {"amax": "1 1", "delayed": "0 1", "none": "0 0"}[mode]
+        text = "".join(f"{M} {N} {K} {CUS} {int(fused)} {int(mx)} {flags}\n" for M, N, K, fused, mx in calls)
         return subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split()
     return of
 
@@ -29,7 +30,22 @@ def kinds(tmp_path_factory):
                                             ("MX", 0, 1), ("MX_INSIDE", 0, 1)])
 def test_the_gpu_tests_reach_the_kernels_they_name(kinds, table, fused, mx):
     entries = getattr(gemm_kinds, table)
-    assert kinds([(*s, fused, mx) for s in entries.values()]) == list(entries)
+    for mode in ("amax", "delayed", "none"):
+        assert kinds([(*s, fused, mx) for s in entries.values()], mode) == list(entries)
+
+
+def test_choices_that_depend_on_the_mode(kinds):
+    """Many small workgroups with a statistic and little K; the fused pair
+    kernel with an intermediate that outgrows the last-level cache."""
+    for K, M, want in ((64, 2048, "big"), (512, 2048, "big"), (1024, 2048, "big"), (1025, 2048, "pair"),
+                       (512, 1536, "big"), (513, 1536, "pair"), (512, 1408, "pair")):
+        assert kinds([(M, 4096, K, 0, 0)], "amax") == kinds([(M, 4096, K, 0, 0)], "delayed") == [want], (M, K)
+        assert kinds([(M, 4096, K, 0, 0)], "none") == kinds([(M, 4096, K, 1, 0)], "amax") == ["pair"], (M, K)
+    assert kinds([(3001, 12288, 5504, 1, 0)], "amax") == ["pair-rounds"]
+    assert kinds([(3001, 12288, 8192, 1, 0)], "amax") == ["fused8-rounds"]
+    assert kinds([(3001, 12288, 8192, 1, 0)], "none") == ["pair-rounds"]
+    assert kinds(list((*s, 0, 0) for s in gemm_kinds.SHORT_K), "amax") == ["big"] * len(gemm_kinds.SHORT_K)
+    assert kinds(list((*s, 0, 0) for s in gemm_kinds.SHORT_K), "none") == ["pair"] * len(gemm_kinds.SHORT_K)
 
 
 def test_tiles_fit_the_kernels(kinds):

@@ -23,6 +23,7 @@ import torch
 
 from paper_2407_17353_amd import binding as sc
 from paper_2407_17353_amd import workloads as wl
+from tests.gemm_kinds import SHORT_K
 from tests.helpers import check_p1, check_p2_full, gpu_matmul, say, stored_with_padding
 
 pytestmark = pytest.mark.gpu
@@ -155,3 +156,25 @@ def test_fused_epilogue_that_fuses_nothing(shape, mode):
         torch.cuda.synchronize()
         res.append((out.data.clone(), out.scale.item(), amax.item()))
     assert torch.equal(res[0][0], res[1][0]) and res[0][1:] == res[1][1:]
+
+
+@pytest.mark.parametrize("shape", [(2100, 4100, 900), (4200, 4200, 900), (1100, 4000, 4500), *SHORT_K],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("ta,tb", [(False, False), (True, True)], ids=["NN", "TT"])
+def test_modes_and_epilogues_sum_in_one_order(shape, ta, tb):
+    """A call may take another kernel with a statistic than without one, and
+    another with a fused epilogue: the accumulators are the same bits."""
+    M, N, K = shape
+    say(f"case one order {shape} ta={ta} tb={tb}")
+    A, B = _operands(M, N, K, 0, 1, ta, tb, 60)
+    a = sc.ScaledArray(stored_with_padding(A, DEV), 0, sc.scale_tensor(2, DEV), ta)
+    b = sc.ScaledArray(stored_with_padding(B, DEV), 1, sc.scale_tensor(-3, DEV), tb)
+    accs = []
+    for kw in ({"rescale": sc.RESCALE_AMAX}, {"rescale": sc.RESCALE_NONE},
+               {"rescale": sc.RESCALE_NONE, "amax_out": torch.zeros(1, device=DEV)},
+               {"rescale": sc.RESCALE_AMAX, "activation": sc.ACT_RELU}):
+        acc = torch.empty((M, N), device=DEV)
+        sc.scalify_matmul(a, b, sc.empty_scaled(M, N, sc.E4M3, DEV), acc_out=acc, **kw)
+        torch.cuda.synchronize()
+        accs.append(acc.view(torch.int32))
+    assert all(torch.equal(accs[0], x) for x in accs[1:])
