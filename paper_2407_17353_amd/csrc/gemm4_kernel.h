@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
       const uint32_t off = grp < groups
                                ? ((uint32_t)(l_kt * groups + grp) * 64u + (uint32_t)lane) * 4u
                                : (uint32_t)r.z;
-      load_lds4(r, off, sS + stage * 2048 + (is_b ? 1024 : 0) + 256 * wave);
+      load_lds4<B_KC && !(A_MN && SP) ? 3 : 0>(r, off, sS + stage * 2048 + (is_b ? 1024 : 0) + 256 * wave);
     }
   };
   auto scale_word = [&](int stage, int half, int j) -> int {
@@ -613,10 +613,6 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
     sb[0][1] = scale_word(0, 1, wn / 64 + 1);
   }
   mfma_drain();
-  if (opens) {
-    wait_vmcnt<0>();  // (its words; the loads before them have landed)
-    header_publish(p);
-  }
 
   using P0 = std::integral_constant<int, 0>;
   using P1 = std::integral_constant<int, 1>;
@@ -624,6 +620,7 @@ __global__ __launch_bounds__(256, 1) void gemm4_kernel(GemmParams p) {
   tile_origin(blockIdx.x, p.tiles_m, p.tiles_n, c_m0, c_n0);
   float lmax = 0.f;
   head(P0{}, 0);
+  if (opens) header_publish(p);  // (its words are older than what the head leaves in flight)
   for (int kt = 0;;) {
     tail(P0{}, kt);
     head(P1{}, kt + 1);

@@ -236,7 +236,7 @@ __global__ __launch_bounds__(512, 1) void gemm8_kernel(GemmParams p) {
       const v4i r = is_b ? make_rsrc(p.mx_b, p.mx_b_bytes) : make_rsrc(p.mx_a, p.mx_a_bytes);
       const uint32_t off =
           grp < groups ? ((uint32_t)(kt * groups + grp) * 64u + (uint32_t)lane) * 4u : (uint32_t)r.z;
-      load_lds4(r, off, sS + stage * 2048 + (is_b ? 1024 : 0) + 256 * (wave & 3));
+      load_lds4<0>(r, off, sS + stage * 2048 + (is_b ? 1024 : 0) + 256 * (wave & 3));
     }
   };
   // This lane's word of tile group j (0..3) of operand half (0 A, 1 B).

@@ -103,19 +103,21 @@ __device__ __forceinline__ void load_lds16(v4i rsrc, uint32_t voff, uint8_t* lds
 }
 
 // One buffer_load_dword ... lds: lane i's 4 bytes land at M0 + 4 i (the
-// MX block-scale staging; same M0 and ordering rules as load_lds16). Its
-// resource is rarely used and may just have been restored from a spill, by a
-// vector instruction: a vector memory instruction may read a scalar register
-// five wait states after that, which the longer s_nop makes sure of.
+// MX block-scale staging; same M0 and ordering rules as load_lds16). A vector
+// memory instruction may read a scalar register five wait states after a vector
+// instruction wrote it (a resource restored from a spill, say): NOP, the wait
+// states after the write of M0 less one, makes sure of it at 3 and costs the
+// block-scaled kernels up to 1 %; 0 where the build check finds no such write.
+template <int NOP>
 __device__ __forceinline__ void load_lds4(v4i rsrc, uint32_t voff, uint8_t* lds_base) {
   const uint32_t lds_addr = (uint32_t)(uintptr_t)(LDS_AS void*)lds_base;
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
   asm volatile(
-      "s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+      "s_mov_b32 m0, %0\n\ts_nop %3\n\t"
       "buffer_load_dword %1, %2, 0 offen lds"
       :
-      : "s"(lds_addr), "v"(voff), "s"(rsrc)
+      : "s"(lds_addr), "v"(voff), "s"(rsrc), "n"(NOP)
       : "memory", "m0");
 #pragma clang diagnostic pop
 }

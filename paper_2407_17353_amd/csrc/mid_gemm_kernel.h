@@ -202,7 +202,7 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
       begin(decltype(I)::value);
       for (int j = 0; j < LPS; ++j) issue_one(j, decltype(I)::value, lds + decltype(I)::value * STAGE);
     });
-    const bool opens = first && t == 0 && header_begin(p, raw_scales);
+    bool opens = first && t == 0 && header_begin(p, raw_scales);
     wait_vmcnt<(S - 2) * LPS>();
     __syncthreads();
     zero_tail(0, lds);
@@ -217,10 +217,6 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
     });
     wait_lgkmcnt<0>();
     mfma_drain();  // (the zeroing, before the first MFMAs read it)
-    if (opens) {
-      wait_vmcnt<LPS>();  // (its words, before the loads of step S - 1)
-      header_publish(p);
-    }
     __builtin_amdgcn_sched_barrier(0);
     int st_i = 0;  // stage of step i
     auto step = [&](auto P, int i) {
@@ -273,6 +269,11 @@ __global__ __launch_bounds__(MD_THREADS, S == 2 ? 2 : 1) void mid_gemm_kernel(Ge
 #pragma unroll 1
     for (int i = 0;;) {
       step(P0{}, i);
+      if (opens) {
+        wait_vmcnt<2 * LPS>();  // (its words, before the loads of two steps)
+        header_publish(p);
+        opens = false;
+      }
       if (++i >= KT) break;
       step(P1{}, i);
       if (++i >= KT) break;

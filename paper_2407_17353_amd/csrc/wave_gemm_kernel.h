@@ -201,8 +201,8 @@ __global__ __launch_bounds__(WV_THREADS, 1) void wave_gemm_kernel(GemmParams p) 
         const v4i xa = make_rsrc(p.mx_a, p.mx_a_bytes), xb = make_rsrc(p.mx_b, p.mx_b_bytes);
         const uint32_t oa = ((uint32_t)(kt * p.mx_groups_a + m0 / 64) * 64u + (uint32_t)lane) * 4u;
         const uint32_t ob = ((uint32_t)(kt * p.mx_groups_b + n0 / 64) * 64u + (uint32_t)lane) * 4u;
-        load_lds4(xa, ok ? oa : (uint32_t)xa.z, slot + ABYTES + BBYTES);
-        load_lds4(xb, ok ? ob : (uint32_t)xb.z, slot + ABYTES + BBYTES + 256);
+        load_lds4<0>(xa, ok ? oa : (uint32_t)xa.z, slot + ABYTES + BBYTES);
+        load_lds4<0>(xb, ok ? ob : (uint32_t)xb.z, slot + ABYTES + BBYTES + 256);
       }
     };
     struct Frags {
