@@ -39,7 +39,8 @@ EVENT_EVERY = 4               # GEMM-bracketing events on every 4th timed call
 FMT_NAME = {0: "e4m3", 1: "e5m2", 2: "f16"}
 GEMM_SOURCES = ("paper_2407_17353_amd/csrc/gemm4_kernel.h", "paper_2407_17353_amd/csrc/gemm_kernel.h",
                 "paper_2407_17353_amd/csrc/gemm_nn.hip", "paper_2407_17353_amd/csrc/ew_util.h",
-                "paper_2407_17353_amd/csrc/codec.h", "paper_2407_17353_amd/csrc/kernels.h")
+                "paper_2407_17353_amd/csrc/codec.h", "paper_2407_17353_amd/csrc/kernels.h",
+                "paper_2407_17353_amd/csrc/call_header.h", "paper_2407_17353_amd/csrc/header_tag.h")
 TRAFFIC_SUMMARY = "profiles/gemm_8192cube_e4m3_hbm_traffic.md"
 
 

@@ -23,8 +23,11 @@
  *
  * Conventions for every entry point
  *   - All data and scale pointers are DEVICE pointers owned by the caller.
- *     The library allocates nothing and keeps no state between calls;
- *     concurrent calls are safe when they use distinct workspaces.
+ *     The library allocates nothing and keeps no data between calls (of a
+ *     process it keeps a counter that numbers the calls, and per device the
+ *     number of compute units and the address of the scratch array of
+ *     scalify_matmul_noalloc); concurrent calls are safe when they use
+ *     distinct workspaces. A workspace may hold anything when a call starts.
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *     default stream). No call synchronises the host or reads a scale back.
  *   - Argument errors are detected on the host before any launch; they return
@@ -249,7 +252,10 @@ size_t scalify_matmul_workspace_size_opts(int64_t M, int64_t N, const scalify_ma
  * multiple of 16 elements (8 for an FP16 out). workspace: device memory of
  * at least scalify_matmul_workspace_size_opts(M, N, opts) bytes (for a call
  * with nothing fused: scalify_matmul_workspace_size(M, N, ...)), 256-byte aligned,
- * not shared with a concurrent call. Determinism: reruns are bit-identical.
+ * not shared with a concurrent call. Determinism: reruns are bit-identical,
+ * and so are a call's accumulators in every mode. The order in which K is
+ * summed depends on M, N and K: a row's accumulators may differ in their last
+ * bits from those of the same row in a call of another size.
  * M, N or K may be 0 (K = 0 gives an all-zero output).
  *
  * AMAX on an output small enough that every workgroup holds its tiles (tiles
@@ -348,8 +354,9 @@ scalify_status scalify_layernorm_fwd(const scalify_scaled_array* x, const float*
                                      int32_t saturate, float* pre_out, void* stream);
 
 /* Bytes of device workspace scalify_layernorm_bwd needs: a 256-byte header
- * plus min(R, 1024) x 2 x D fp32 partial parameter gradients. 0 for invalid
- * sizes (D > 8192). */
+ * plus, in fp32, 4 numbers per row and 2 x D (rounded up to 16) partial
+ * parameter gradients per 32 rows (at least once). 0 for invalid sizes
+ * (D > 8192). */
 size_t scalify_layernorm_bwd_workspace_size(int64_t R, int64_t D);
 
 /* Input gradient of scalify_layernorm_fwd with its dynamic rescale (the

@@ -154,7 +154,7 @@ __device__ __forceinline__ void ln_decode16(const uint32_t* w, float (&x)[16]) {
 // that holds an element of the row stays in the row's padding (ld).
 // (Element loads there, whose sixteen tests every wave went through for the
 // lanes past the end as well, took the forward of 16384 x 512 F16 25 us, the
-// backward of 16384 x 2512 F16 147; now 16 and 108.)
+// backward of 16384 x 2512 F16 147; now 16 and 99.)
 template <int F>
 constexpr int ln_chunk_words() { return F == kF32 ? 16 : (F == kF16 ? 8 : 4); }
 

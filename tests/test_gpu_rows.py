@@ -45,8 +45,8 @@ def test_single_read_equals_multi_pass(D, fx, fd, fo, monkeypatch):
 
 
 # more rows than the grid has places (768 or 1024 workgroups of 1, 2 or 4 rows
-# on 256 CUs): the next row's loads, the reuse of the sums' LDS slots and the
-# statistic's early fold (more than two rounds of rows), by waves per row
+# on 256 CUs): the next row's loads and the reuse of the sums' LDS slots, by
+# waves per row
 @pytest.mark.parametrize("R,D", [(6300, 72), (6200, 2048), (3200, 2049), (3100, 4096), (1700, 4100), (1600, 8192)])
 @pytest.mark.parametrize("fx,fd,fo", [(sc.F16, sc.E5M2, sc.E5M2), (sc.F32, sc.F16, sc.F16)], ids=["f16-e5m2", "f32-f16"])
 def test_single_read_equals_multi_pass_over_many_rows(R, D, fx, fd, fo, monkeypatch):
