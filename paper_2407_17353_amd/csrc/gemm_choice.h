@@ -36,7 +36,10 @@ struct GemmChoice {
 //   with one more tile per CU it loses, 512x4096x1024 (512) 23.2 / 15.7.
 //   Block scales, which the 128-row kernel does not have, take it up to two
 //   tiles per CU, against 256 x 256 tiles: 512x4096x4096 34.5 / 53.6, but
-//   1024x4096x1024 (1024) 35.3 / 25.0.
+//   1024x4096x1024 (1024) 35.3 / 25.0. Not the last of them while K is too short
+//   for the split: 2048x1024xK (512), K 64 20.9 / 17.9, 256 21.2 / 17.9 (without
+//   rescale 15.9 / 15.8), 512 22.6 / 20.3 (15.8 / 17.4); 384x4096x256 (384) 17.8
+//   / 19.5.
 // - Up to one 128 x 256 tile per CU: the 128-row kernel, a 256 x 256 grid
 //   leaving half the chip idle. 128 x 128 tiles, two workgroups to a CU, while
 //   K is short: 1024x4096x1024 19.4 against 20.9 of 128 x 256 and 23.4 of
@@ -73,6 +76,7 @@ inline GemmChoice gemm_choice(int64_t M, int64_t N, int64_t K, int cus, bool fus
   const GemmChoice mid8 = make(GEMM_MID, kMidTM, 256, MID_256);
   const GemmChoice mid4 = make(GEMM_MID, kMidTM, 128, MID_128);
   const GemmChoice pair = make(GEMM_MID, kMidTM, 128, MID_128_PAIR);
+  if (mx && K <= 256 && 4 * wave.tiles > 7 * cus) return big;
   if (mx) return wave.tiles <= kWaveHeld * cus ? wave : big;
   if (wave.tiles <= cus) return wave;
   if (mid8.tiles <= cus && !fused && statistic &&

@@ -16,7 +16,7 @@ PLAIN_INSIDE = {"wave": (512, 384, 256), "big": (2304, 4096, 256)}
 FUSED = {"pair": (700, 1500, 255), "mid128": (700, 1500, 4100), "mid256": (1100, 4000, 4100),
          "pair-rounds": (4100, 4200, 400), "fused8": (2100, 4100, 200)}
 # with block scales
-MX = {"wave-rounds": (900, 2100, 200), "big": (1100, 2100, 200), "big-rounds": (4200, 4200, 200)}
-MX_INSIDE = {"wave-rounds": (512, 4096, 256), "big": (1280, 2304, 512)}
+MX = {"wave-rounds": (800, 2100, 200), "big": (1100, 2100, 200), "big-rounds": (4200, 4200, 200)}
+MX_INSIDE = {"wave-rounds": (384, 4096, 256), "big": (1280, 2304, 512)}
 # plain calls: big with a statistic, pair without one
 SHORT_K = [(2048, 4096, 400), (2000, 4000, 250)]

@@ -44,6 +44,10 @@ def test_choices_that_depend_on_the_mode(kinds):
     assert kinds([(3001, 12288, 5504, 1, 0)], "amax") == ["pair-rounds"]
     assert kinds([(3001, 12288, 8192, 1, 0)], "amax") == ["fused8-rounds"]
     assert kinds([(3001, 12288, 8192, 1, 0)], "none") == ["pair-rounds"]
+    # (block scales, whose kernels sum K differently, in no mode)
+    for K, M, want in ((64, 2048, "big"), (256, 1856, "big"), (257, 2048, "wave-rounds"), (256, 1792, "wave-rounds")):
+        for mode in ("amax", "delayed", "none"):
+            assert kinds([(M, 1024, K, 0, 1)], mode) == [want], (M, K, mode)
     assert kinds(list((*s, 0, 0) for s in gemm_kinds.SHORT_K), "amax") == ["big"] * len(gemm_kinds.SHORT_K)
     assert kinds(list((*s, 0, 0) for s in gemm_kinds.SHORT_K), "none") == ["pair"] * len(gemm_kinds.SHORT_K)
 
